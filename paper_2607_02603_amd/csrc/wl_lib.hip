@@ -1615,8 +1615,7 @@ int verify_run(const wl_csr* g, const uint32_t* color, uint32_t k, uint8_t* ws,
   if (h.err & kVErrColor) return fail(WL_EINVAL, "a colour is >= k");
   hipLaunchKernelGGL(k_v_multi<K>, dim3(gn), dim3(kBlock), 0, s, v);
   hipLaunchKernelGGL(k_v_bin<K>, dim3(gn), dim3(kBlock), 0, s, v);
-  hipLaunchKernelGGL(k_v_sort_wave<K>, dim3(grid_for(v.n, kBlock / kWave, 8192)),
-                     dim3(kBlock), 0, s, v);
+  hipLaunchKernelGGL(k_v_sort_wave<K>, dim3(gn), dim3(kBlock), 0, s, v);
   HIP_LAUNCH_CHECK();
   if (int r = pull()) return r;
   if (h.n_mid)
@@ -1636,8 +1635,7 @@ int verify_run(const wl_csr* g, const uint32_t* color, uint32_t k, uint8_t* ws,
     }
   }
   if constexpr (sizeof(K) == 4)
-    hipLaunchKernelGGL(k_v_compare, dim3(grid_for(v.n, kBlock / 16, 8192)), dim3(kBlock), 0,
-                       s, v);
+    hipLaunchKernelGGL(k_v_compare, dim3(gn), dim3(kBlock), 0, s, v);
   else
     hipLaunchKernelGGL(k_v_compare_w, dim3(gn), dim3(kBlock), 0, s, v);
   HIP_LAUNCH_CHECK();

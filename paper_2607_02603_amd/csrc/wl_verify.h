@@ -5,13 +5,14 @@
 // Every row that matters (a row of a class with two or more nodes) becomes
 // its sorted list of neighbour colours, kept in CSR layout in 'keys'; for
 // weighted graphs the entry weight rides in the low 32 bits of a 64-bit key.
-// Each node is then compared with the smallest node of its class:
+// Each node is then compared with one representative node of its class:
 //   unweighted  the sorted colour lists must be equal (equal multisets);
 //   weighted    the lists of (colour, summed weight) runs must be equal,
 //               runs whose weights sum to zero being absent (an entry of
 //               weight 0 adds nothing to a_{i,B}).
 // Row sorts:
-//   <= 64 entries         bitonic network across the lanes of one wave;
+//   <= 64 entries         networks in the registers of one lane (8 entries),
+//                         across 16 lanes (16) or across a wave;
 //   <= kVChunk entries    bitonic network in LDS, one workgroup per row;
 //   longer rows           every aligned chunk of kVChunk entries is sorted in
 //                         LDS, then the chunks are merged in place by the
@@ -48,7 +49,7 @@ struct VerCtx {
   const uint32_t* wgt;
   const uint32_t* color;
   VerState* st;
-  uint32_t* rep;        // k: smallest node of each class
+  uint32_t* rep;        // k: a node of each class
   uint8_t* multi;       // k: 1 if the class has two or more nodes
   uint32_t* mid;        // rows to sort in LDS
   uint32_t* hub;        // rows longer than kVChunk
@@ -96,17 +97,33 @@ __global__ void __launch_bounds__(kBlock) k_v_clear(VerCtx<K> v) {
   }
 }
 
-// Representative of every class: its smallest node.
+// Representative of every class: one of its nodes (any: the comparison below
+// is an equivalence).  A node that finds no representative yet stores itself,
+// and the last store stays; the store is at agent scope, so that all XCDs see
+// the same one afterwards.  Bound by the accesses to one address that a big
+// class makes: each workgroup remembers the classes it has met in a small
+// direct-mapped table and stores once for each.  R-MAT 22 (4.2e6 nodes, half
+// of them in one class): an atomic minimum per node 2.7 ms, a store per node
+// that sees none 0.33 ms, this 0.28 ms (the 2.0e6 scattered stores of the
+// other classes).
+constexpr uint32_t kVSeen = 1024;
 template <typename K>
 __global__ void __launch_bounds__(kBlock) k_v_rep(VerCtx<K> v) {
+  __shared__ uint32_t seen[kVSeen];
+  for (uint32_t t = threadIdx.x; t < kVSeen; t += kBlock) seen[t] = 0xFFFFFFFFu;
+  __syncthreads();
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < v.n; i += gridDim.x * kBlock) {
     const uint32_t c = v.color[i];
     if (c >= v.k) {
       atomicOr(&v.st->err, kVErrColor);
       continue;
     }
-    if (__hip_atomic_load(&v.rep[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > i)
-      atomicMin(&v.rep[c], i);
+    // colours are below k <= 2^32 - 1: no colour is the empty mark.  A racing
+    // write of another class only costs a store more.
+    if (seen[c % kVSeen] == c) continue;
+    seen[c % kVSeen] = c;
+    if (v.rep[c] == 0xFFFFFFFFu)
+      __hip_atomic_store(&v.rep[c], i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -143,28 +160,87 @@ __global__ void __launch_bounds__(kBlock) k_v_bin(VerCtx<K> v) {
   }
 }
 
-// One wave per row of 1 .. 64 entries: keys, bitonic sort across lanes.
+// Ascending bitonic sort of one key per lane inside aligned groups of G lanes.
+template <int G, typename K>
+__device__ __forceinline__ K group_bitonic(K key, uint32_t lane) {
+#pragma unroll
+  for (uint32_t kk = 2; kk <= (uint32_t)G; kk <<= 1) {
+#pragma unroll
+    for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
+      const K pk = __shfl_xor(key, (int)j, kWave);
+      const bool up = (lane & kk & (G - 1)) == 0;
+      const bool lower = (lane & j) == 0;
+      if ((lower == up) ? (pk < key) : (pk > key)) key = pk;
+    }
+  }
+  return key;
+}
+
+// Lane of the r-th set bit of m (r from 0; 64 when there are fewer).
+__device__ __forceinline__ int nth_bit(unsigned long long m, int r) {
+  for (; r > 0 && m; --r) m &= m - 1;
+  return m ? __builtin_ctzll(m) : kWave;
+}
+
+constexpr uint32_t kVLane = 8;    // rows sorted by one lane in registers
+constexpr uint32_t kVGroup = 16;  // ... by 16 lanes; longer ones (<= 64) by the wave
+
+// Rows of 1 .. 64 entries.  A wave takes 64 consecutive nodes, one per lane,
+// so the colours and row pointers are read coalesced; most nodes of a
+// refined graph are alone in their class or have no entry, and a wave per
+// node spent its time on finding that out (R-MAT 22: 0.56 ms, now 0.04 ms).
+// Rows of at most 8 entries are sorted by their lane (a 19-comparator
+// network), rows of up to 16 four at a time, the others one at a time.
 template <typename K>
 __global__ void __launch_bounds__(kBlock) k_v_sort_wave(VerCtx<K> v) {
   const uint32_t lane = lane_id();
-  const uint32_t nwaves = gridDim.x * (kBlock / kWave);
-  for (uint32_t i = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; i < v.n;
-       i += nwaves) {
-    if (!v.multi[v.color[i]]) continue;
-    const uint64_t b = v_beg(v, i), len = v_beg(v, i + 1) - b;
-    if (len == 0 || len > (uint64_t)kWave) continue;
-    K key = lane < len ? v_key(v, b + lane) : v_inf<K>();
-#pragma unroll
-    for (uint32_t kk = 2; kk <= (uint32_t)kWave; kk <<= 1) {
-#pragma unroll
-      for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-        const K pk = __shfl_xor(key, (int)j, kWave);
-        const bool up = (lane & kk) == 0;
-        const bool lower = (lane & j) == 0;
-        if ((lower == up) ? (pk < key) : (pk > key)) key = pk;
-      }
+  const uint64_t step = (uint64_t)gridDim.x * kBlock;
+  // 'base' is the same for all lanes of a wave (the shuffles need them all)
+  for (uint64_t base = blockIdx.x * (uint64_t)kBlock + threadIdx.x - lane; base < v.n;
+       base += step) {
+    const uint64_t i = base + lane;
+    uint64_t b = 0, len = 0;
+    if (i < v.n && v.multi[v.color[i]]) {
+      b = v_beg(v, (uint32_t)i);
+      len = v_beg(v, (uint32_t)i + 1) - b;
     }
-    if (lane < len) v.keys[b + lane] = key;
+    if (len >= 1 && len <= kVLane) {
+      K s[kVLane];
+#pragma unroll
+      for (uint32_t u = 0; u < kVLane; ++u) s[u] = u < len ? v_key(v, b + u) : v_inf<K>();
+      // Batcher's odd-even merge sort of eight
+      constexpr int net[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6},
+                                  {5, 7}, {1, 2}, {5, 6}, {0, 4}, {1, 5}, {2, 6}, {3, 7},
+                                  {2, 4}, {3, 5}, {1, 2}, {3, 4}, {5, 6}};
+#pragma unroll
+      for (int c = 0; c < 19; ++c) {
+        const K x = s[net[c][0]], y = s[net[c][1]];
+        s[net[c][0]] = x < y ? x : y;
+        s[net[c][1]] = x < y ? y : x;
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kVLane; ++u)
+        if (u < len) v.keys[b + u] = s[u];
+    }
+    const uint32_t g = lane / kVGroup, sub = lane % kVGroup;
+    unsigned long long m = __ballot(len > kVLane && len <= kVGroup);
+    while (m) {
+      const int l = nth_bit(m, (int)g);
+      const uint64_t rb = __shfl(b, l & (kWave - 1), kWave);
+      uint64_t rl = __shfl(len, l & (kWave - 1), kWave);
+      if (l == kWave) rl = 0;  // fewer rows left than groups
+      K key = sub < rl ? v_key(v, rb + sub) : v_inf<K>();
+      key = group_bitonic<(int)kVGroup>(key, lane);
+      if (sub < rl) v.keys[rb + sub] = key;
+      for (uint32_t t = 0; t < kWave / kVGroup; ++t) m &= m - 1;
+    }
+    for (m = __ballot(len > kVGroup && len <= (uint64_t)kWave); m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const uint64_t rb = read_lane64(b, l), rl = read_lane64(len, l);
+      K key = lane < rl ? v_key(v, rb + lane) : v_inf<K>();
+      key = group_bitonic<kWave>(key, lane);
+      if (lane < rl) v.keys[rb + lane] = key;
+    }
   }
 }
 
@@ -343,22 +419,37 @@ __global__ void __launch_bounds__(kBlock) k_v_hub_finish(VerCtx<K> v, uint64_t k
   }
 }
 
-// Unweighted: 16 lanes per node compare its sorted list with its
-// representative's.
+// Unweighted: every node's sorted list against its representative's, one
+// node per lane (coalesced colours and row pointers; R-MAT 22: 0.21 ms with 16
+// lanes per node, now 0.05 ms); lists of more than kVLane entries are compared by the
+// whole wave, one node after the other.
 __global__ void __launch_bounds__(kBlock) k_v_compare(VerCtx<uint32_t> v) {
-  constexpr uint32_t G = 16;
-  const uint32_t sub = threadIdx.x % G;
-  const uint32_t ngroups = gridDim.x * (kBlock / G);
-  for (uint32_t i = blockIdx.x * (kBlock / G) + threadIdx.x / G; i < v.n; i += ngroups) {
-    const uint32_t c = v.color[i];
-    const uint32_t r = v.rep[c];
-    if (r == i) continue;
-    const uint64_t bi = v_beg(v, i), li = v_beg(v, i + 1) - bi;
-    const uint64_t br = v_beg(v, r), lr = v_beg(v, r + 1) - br;
-    bool bad = li != lr;
-    if (!bad)
-      for (uint64_t t = sub; t < li; t += G)
+  const uint32_t lane = lane_id();
+  const uint64_t step = (uint64_t)gridDim.x * kBlock;
+  for (uint64_t base = blockIdx.x * (uint64_t)kBlock + threadIdx.x - lane; base < v.n;
+       base += step) {
+    const uint64_t i = base + lane;
+    uint64_t bi = 0, li = 0, br = 0;
+    bool bad = false;
+    if (i < v.n) {
+      const uint32_t r = v.rep[v.color[i]];
+      if (r != (uint32_t)i) {
+        bi = v_beg(v, (uint32_t)i);
+        li = v_beg(v, (uint32_t)i + 1) - bi;
+        br = v_beg(v, r);
+        bad = li != v_beg(v, r + 1) - br;
+        if (bad) li = 0;
+      }
+    }
+    if (li <= kVLane)
+      for (uint32_t t = 0; t < (uint32_t)li; ++t)
         if (v.keys[bi + t] != v.keys[br + t]) bad = true;
+    for (unsigned long long m = __ballot(li > kVLane); m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const uint64_t wb = read_lane64(bi, l), wl = read_lane64(li, l), wr = read_lane64(br, l);
+      for (uint64_t t = lane; t < wl; t += kWave)
+        if (v.keys[wb + t] != v.keys[wr + t]) bad = true;
+    }
     if (bad) atomicOr(&v.st->err, kVErrMismatch);
   }
 }

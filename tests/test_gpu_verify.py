@@ -117,6 +117,18 @@ def test_long_rows_every_sort_path(deg):
     assert not _agree(rp, col, None, c)
 
 
+@pytest.mark.parametrize("deg", [1, 2, 7, 8, 9, 15, 16, 17, 33, 63, 64])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_short_rows_every_sort_path(deg, weighted):
+    # 70 hubs: more rows than lanes of a wave, and a last group that is not full
+    rng = random.Random(deg)
+    for mutate in (None, "one_colour"):
+        rp, col, c = _hub_graph(rng, [deg] * 70, 5, mutate=mutate)
+        wt = np.full(col.size, 3, np.uint32) if weighted else None
+        _say(f"rows of {deg} weighted={weighted} {mutate}")
+        assert _agree(rp, col, wt, c) == (mutate is None)
+
+
 def test_many_hubs_of_mixed_lengths():
     # one class per length, 3 hubs each: every merge stage runs with rows
     # of different padded lengths side by side
