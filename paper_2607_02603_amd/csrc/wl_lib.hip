@@ -510,49 +510,69 @@ __global__ void __launch_bounds__(kBlock) k_count_colors(Ctx ctx, uint32_t k) {
        i += gridDim.x * kBlock)
     ctx.ids[i] = 0;
 }
-// Class sizes of a given colouring.  The lanes of a wave that share a colour
-// add their count with one atomic (a colouring with few classes would
-// otherwise put most atomics of the device on one address).
+// Class sizes of a given colouring (ids), and every node's rank inside its
+// class (in perm_tmp), so that the placement needs no second round of
+// atomics.  A workgroup gathers the classes of kColorTile nodes in an LDS hash
+// table (at most half full, so every probe ends) whose counters give the ranks
+// inside the tile, and adds each class's count with one global atomic: a class
+// with most of the nodes takes one atomic per tile, and a tile of classes of
+// one node each takes them all at once.  R-MAT 22 in about 10^6 classes: one
+// atomic per distinct colour of a wave, peeled one by one, 0.78 ms for the
+// sizes and 0.79 ms for the placement; this 0.37 ms and 0.04 ms.
+constexpr uint32_t kColorTile = 4 * kBlock, kColorSlots = 2 * kColorTile;
 __global__ void __launch_bounds__(kBlock) k_hist_colors(Ctx ctx) {
-  const uint32_t lane = lane_id();
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ctx.n;
-       i += gridDim.x * kBlock) {
-    const uint32_t c = ctx.c[i];
-    const unsigned long long peers = wave_peers(c, true);
-    if ((int)lane == __ffsll((long long)peers) - 1)
-      atomicAdd(&ctx.ids[c], (uint32_t)__popcll(peers));
-  }
-}
-// One block: cstart = exclusive scan of ids[0..k]; ids becomes the cursor.
-__global__ void __launch_bounds__(kBlock) k_scan_colors(Ctx ctx, uint32_t k) {
-  __shared__ uint32_t sh[kBlock / kWave];
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base <= k; base += kBlock) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t v = i <= k ? ctx.ids[i] : 0;
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan(v, sh, &tot);
-    if (i <= k) {
-      ctx.cstart[i] = carry + ex;
-      ctx.ids[i] = carry + ex;
+  __shared__ uint32_t key[kColorSlots];
+  __shared__ uint32_t cnt[kColorSlots];
+  constexpr uint32_t kPer = kColorTile / kBlock;
+  for (uint64_t b0 = (uint64_t)blockIdx.x * kColorTile; b0 < ctx.n;
+       b0 += (uint64_t)gridDim.x * kColorTile) {
+    uint32_t c[kPer], slot[kPer], rank[kPer];
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+      const uint64_t i = b0 + u * kBlock + threadIdx.x;
+      c[u] = i < ctx.n ? ctx.c[i] : 0xFFFFFFFFu;  // no colour: colours are below k <= n
     }
-    carry += tot;
+    for (uint32_t t = threadIdx.x; t < kColorSlots; t += kBlock) {
+      key[t] = 0xFFFFFFFFu;
+      cnt[t] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+      if (c[u] == 0xFFFFFFFFu) continue;
+      uint32_t s = (c[u] * 0x9E3779B1u) >> 21;
+      static_assert(kColorSlots == 1u << 11, "hash to a slot");
+      while (true) {
+        const uint32_t old = atomicCAS(&key[s], 0xFFFFFFFFu, c[u]);
+        if (old == 0xFFFFFFFFu || old == c[u]) break;
+        s = (s + 1) & (kColorSlots - 1);
+      }
+      slot[u] = s;
+      rank[u] = atomicAdd(&cnt[s], 1u);
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < kColorSlots; t += kBlock)
+      if (cnt[t]) cnt[t] = atomicAdd(&ctx.ids[key[t]], cnt[t]);  // the tile's first rank
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u)
+      if (c[u] != 0xFFFFFFFFu)
+        ctx.perm_tmp[b0 + u * kBlock + threadIdx.x] = cnt[slot[u]] + rank[u];
+    __syncthreads();
   }
 }
-// Nodes grouped by colour: one cursor reservation per colour present in a
-// wave, the lanes' slots by their position among its peers.
+// cstart = the scanned class sizes (ids).
+__global__ void __launch_bounds__(kBlock) k_starts_colors(Ctx ctx, uint32_t k) {
+  for (uint32_t b = blockIdx.x * kBlock + threadIdx.x; b <= k; b += gridDim.x * kBlock)
+    ctx.cstart[b] = b < k ? ctx.ids[b] : ctx.n;
+}
+// Nodes grouped by colour.
 __global__ void __launch_bounds__(kBlock) k_place_colors(Ctx ctx) {
-  const uint32_t lane = lane_id();
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ctx.n;
-       i += gridDim.x * kBlock) {
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ctx.n; i += gridDim.x * kBlock) {
     const uint32_t c = ctx.c[i];
-    const unsigned long long peers = wave_peers(c, true);
-    const int ldr = __ffsll((long long)peers) - 1;
-    uint32_t at = 0;
-    if ((int)lane == ldr) at = atomicAdd(&ctx.ids[c], (uint32_t)__popcll(peers));
-    at = __shfl(at, ldr, kWave) + (uint32_t)__popcll(peers & ((1ull << lane) - 1));
-    ctx.perm[at] = i;
-    ctx.act[i] = (ctx.cstart[c + 1] - ctx.cstart[c]) >= 2 ? 1 : 0;
+    const uint32_t s = ctx.cstart[c];
+    ctx.perm[s + ctx.perm_tmp[i]] = i;
+    ctx.act[i] = ctx.cstart[c + 1] - s >= 2 ? 1 : 0;
   }
 }
 
@@ -1766,7 +1786,10 @@ int wl_refine_round(const wl_csr* g, const uint32_t* color_in, uint32_t k_in,
   hipLaunchKernelGGL(k_count_colors, dim3(grid_for(k_in + 1)), dim3(kBlock), 0, S.s,
                      S.ctx, k_in);
   hipLaunchKernelGGL(k_hist_colors, dim3(gn), dim3(kBlock), 0, S.s, S.ctx);
-  hipLaunchKernelGGL(k_scan_colors, dim3(1), dim3(kBlock), 0, S.s, S.ctx, k_in);
+  // the class starts by the device-wide scan over the k_in sizes (st->k)
+  S.xscan(nullptr, &S.ctx.st->k, S.ctx.ids, nullptr, nullptr, nullptr, scan_blocks(k_in));
+  hipLaunchKernelGGL(k_starts_colors, dim3(grid_for(k_in + 1ull, kBlock, 4096)), dim3(kBlock), 0,
+                     S.s, S.ctx, k_in);
   hipLaunchKernelGGL(k_place_colors, dim3(gn), dim3(kBlock), 0, S.s, S.ctx);
   HIP_LAUNCH_CHECK();
   if (int r = S.stats_begin()) return r;

@@ -206,6 +206,24 @@ def test_refine_round_sparse_colour_ids():
     assert kg == k2 and np.array_equal(cout.cpu().numpy().view(np.uint32), c2)
 
 
+@pytest.mark.parametrize("n", [1, 2, 255, 1023, 1024, 1025, 2049, 9001])
+@pytest.mark.parametrize("shape", ["one", "half", "discrete"])
+def test_refine_round_class_sizes(n, shape):
+    # one class, one class with half of the nodes beside classes of one node
+    # each, and only those: the grouping by colour takes tiles of 1024 nodes
+    g = inputs.csr_from_edges(n, np.arange(n - 1), np.arange(1, n))
+    rng = np.random.default_rng(n)
+    c = rng.permutation(n).astype(np.uint32)
+    if shape != "discrete":
+        c[rng.random(n) < (2 if shape == "one" else 0.5)] = n // 2
+    _say(f"n={n} {shape}")
+    dg = _dev_graph(g.row_ptr, g.col)
+    cin = torch.from_numpy(c.view(np.int32)).cuda()
+    cout, kg = wl.wl_refine_round(dg, cin, n, 11, 1)
+    c2, k2, _ = oracle.refine_round(g.row_ptr, g.col, None, c, n, 11, 1)
+    assert kg == k2 and np.array_equal(cout.cpu().numpy().view(np.uint32), c2)
+
+
 # ---------------------------------------------------------------------------
 # configurations
 # ---------------------------------------------------------------------------
