@@ -351,6 +351,10 @@ int wl_stats_get(wl_stats *out);
  *                        (default: on when at least half the entries feed
  *                        rows whose image is needed).
  *   WL_DEGREE_ROUND=0    no histogram round from one colour.
+ *   WL_SMALL=0           graphs of at most 4096 nodes and 2^17 entries take
+ *                        the general path too, not the one-workgroup one (as
+ *                        they do while WL_VALIDATE or a tuning variable of
+ *                        the in-core rounds is set, or wl_stats is enabled).
  *   WL_HOST_ROUNDS=n     rounds driven from the host before the device-driven
  *                        ones (default 8).
  *   WL_ASYNC_PASSES=n    radix passes a device-driven round launches (0-8).

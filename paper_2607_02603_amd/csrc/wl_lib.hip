@@ -36,6 +36,7 @@
 #include "wl_stream.h"
 #include "wl_spmv.h"
 #include "wl_push.h"
+#include "wl_small.h"
 #include "wl_quotient.h"
 #include "wl_verify.h"
 
@@ -803,9 +804,12 @@ struct Session {
       hipLaunchKernelGGL(k_ring_rows<uint32_t>, dim3(g), dim3(kBlock), 0, s, ctx);
     HIP_LAUNCH_CHECK();
     if (int r = pull()) return r;
-    if (host.err & kErrRowSum)
-      return fail(WL_EOVERFLOW, "a row sum exceeds 2^32, the bound of arithmetic mod 2^64");
+    if (host.err & kErrRowSum) return fail_row_sum();
     return WL_OK;
+  }
+
+  static int fail_row_sum() {
+    return fail(WL_EOVERFLOW, "a row sum exceeds 2^32, the bound of arithmetic mod 2^64");
   }
 
   // The sorting networks (one launch: gt workgroups for the tiny segments,
@@ -1512,6 +1516,51 @@ struct Session {
     return WL_OK;
   }
 
+  // A graph that one workgroup's LDS holds goes through wl_small.h whole: the
+  // general path takes 0.6 ms or more for any graph, this one 0.05 ms for
+  // 1500 nodes and 12,000 entries.  The bounds are the LDS (nodes) and where
+  // one compute unit's loads of the columns cost as much as the general
+  // path's launches (entries).  WL_SMALL=0, the tuning variables of the
+  // general path, validation and the diagnostics (which describe its image
+  // launches) keep a graph on the general path.
+  bool small_applies(bool diag) const {
+    if (L.n > kSmallNodes || L.nnz > kSmallEntries || (diag && g_stats_flags)) return false;
+    static const char* const names[] = {"WL_VALIDATE",    "WL_PB",          "WL_DEGREE_ROUND",
+                                        "WL_HOST_ROUNDS", "WL_ASYNC_PASSES", "WL_GRAPH",
+                                        "WL_NT_STREAM",   "WL_SORT_FIX",     "WL_CHAIN_SPINS"};
+    for (const char* v : names)
+      if (getenv(v)) return false;
+    return env_int("WL_SMALL", 0, 1, 1) != 0;
+  }
+
+  template <bool RP64, bool W>
+  void small_launch(const SmallArgs& a) {
+    if (L.nnz <= kSmallLdsEntries)
+      hipLaunchKernelGGL((k_small<RP64, W, true>), dim3(1), dim3(kSmallThreads), 0, s, ctx, a);
+    else
+      hipLaunchKernelGGL((k_small<RP64, W, false>), dim3(1), dim3(kSmallThreads), 0, s, ctx, a);
+  }
+
+  int run_small(const uint32_t* init_dev, uint64_t seed, uint32_t max_rounds, bool diag) {
+    const SmallArgs a{init_dev, seed, max_rounds};
+    if (rp64) {
+      if (weighted) small_launch<true, true>(a); else small_launch<true, false>(a);
+    } else {
+      if (weighted) small_launch<false, true>(a); else small_launch<false, false>(a);
+    }
+    HIP_LAUNCH_CHECK();
+    if (int r = pull()) return r;
+    if (host.err == kErrSmallNnz)
+      return fail(WL_EINVAL, "row_ptr[n] does not equal nnz = %llu", (unsigned long long)L.nnz);
+    if (host.err == kErrSmallRow) return fail_row_sum();
+    if (diag) {
+      stats = wl_stats{};
+      stats.rounds = host.round;
+      g_stats = stats;
+    }
+    return WL_OK;
+  }
+
   int round() {
     hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(1), 0, s, ctx);
     if (int r = spmv()) return r;
@@ -1576,6 +1625,26 @@ int open_session(Session& S, const wl_csr* g, uint32_t* colors, void* ws,
     }
   }
   return WL_OK;
+}
+
+// Algorithm 1 on the opened session's device graph; the result is in S.host
+// and the colours in ctx.c.  diag: record the wl_stats diagnostics.
+int run_in_core(Session& S, const wl_csr* g, const uint32_t* init, uint64_t seed,
+                uint32_t max_rounds, bool diag) {
+  const uint32_t cap =
+      max_rounds ? max_rounds : (uint32_t)std::min<uint64_t>(g->n + 1, 0xFFFFFFFFull);
+  if (S.small_applies(diag)) return S.run_small(init, seed, cap, diag);
+  if (int r = check_nnz_device(g, S.s)) return r;
+  if (int r = S.init_state(seed, 1, 0, cap, 1)) return r;
+  if (int r = S.validate_device()) return r;
+  if (int r = S.check_ring()) return r;
+  if (!diag) {
+    if (int r = S.run_rsc(init)) return r;
+    return S.pull();
+  }
+  if (int r = S.stats_begin()) return r;
+  if (int r = S.run_rsc(init)) return r;
+  return S.stats_end();
 }
 
 #include "wl_outofcore.h"
@@ -1813,14 +1882,7 @@ int wl_stable_coloring(const wl_csr* g, const uint32_t* init_color, uint64_t see
   if (!color_out) return fail(WL_EINVAL, "color_out is NULL");
   Session S;
   if (int r = open_session(S, g, color_out, workspace, ws_bytes, stream)) return r;
-  if (int r = check_nnz_device(g, S.s)) return r;
-  const uint32_t cap = max_rounds ? max_rounds : (uint32_t)std::min<uint64_t>(g->n + 1, 0xFFFFFFFFull);
-  if (int r = S.init_state(seed, 1, 0, cap, 1)) return r;
-  if (int r = S.validate_device()) return r;
-  if (int r = S.check_ring()) return r;
-  if (int r = S.stats_begin()) return r;
-  if (int r = S.run_rsc(init_color)) return r;
-  if (int r = S.stats_end()) return r;
+  if (int r = run_in_core(S, g, init_color, seed, max_rounds, true)) return r;
   *k_out = S.host.k;
   *rounds_out = S.host.round;
   if (S.host.done == 2)
@@ -1859,13 +1921,7 @@ int wl_stable_coloring_noalloc(const wl_csr* g, const uint32_t* init_color, uint
   Session S;
   if (int r = open_session(S, g, color_out, ws, WL_NOALLOC_SCRATCH_BYTES, stream)) return r;
   S.use_graph = false;  // no graph objects: nothing is created
-  if (int r = check_nnz_device(g, S.s)) return r;
-  const uint32_t cap = max_rounds ? max_rounds : (uint32_t)std::min<uint64_t>(g->n + 1, 0xFFFFFFFFull);
-  if (int r = S.init_state(seed, 1, 0, cap, 1)) return r;
-  if (int r = S.validate_device()) return r;
-  if (int r = S.check_ring()) return r;
-  if (int r = S.run_rsc(init_color)) return r;
-  if (int r = S.pull()) return r;
+  if (int r = run_in_core(S, g, init_color, seed, max_rounds, false)) return r;
   *k_out = S.host.k;
   *rounds_out = S.host.round;
   if (S.host.done == 2)
