@@ -66,6 +66,11 @@ struct DevState {
   uint32_t n_pico;      // segments of <= kPicoMax nodes (this round)
   uint32_t n_msort;     // segments of kTinyMax + 1 .. kMidMax nodes (this round)
   uint32_t tickets[4];  // chunk tickets of this round's chained scans (per site)
+  uint32_t max_len;     // members of the largest live class of the current round when
+                        // they are more than kSmallMax, else 0
+  uint32_t max_len2;    // the same for the next round
+  uint32_t npass;       // most radix passes that a round of the call had work for
+  uint32_t label_max;   // largest initial label
   uint64_t seed;
   // The two big-segment lists: (entries << 32) | tiles.  One 64-bit atomic
   // appends a segment and reserves its tiles, so the tile offsets come out
@@ -73,8 +78,13 @@ struct DevState {
   unsigned long long big[2];
   unsigned long long work[3][2];    // diagnostics: rows, entries per image kind
   unsigned long long act_entries;   // entries of the rows whose image is needed
+  unsigned long long live_entries;  // entries of the live rows when the live classes are set up
   unsigned long long sym_hash[2];   // validation: hashes of (i, j) and (j, i)
 };
+
+// DevState::err bits seen before any column or weight is read.
+constexpr uint32_t kErrRowSum = 32u;  // a row sum above 2^32 (ring)
+constexpr uint32_t kErrNnz = 128u;    // row_ptr[n] is not nnz
 
 struct HeavyChunk {
   uint64_t beg;   // first entry
@@ -136,6 +146,7 @@ struct Ctx {
   int weighted;
   uint32_t ring;       // 0: image in F_p (p = 2^61 - 1); 1: in Z/2^64 (wl_device.h)
   int nt_stream;       // stream col_idx with non-temporal loads
+  int key_bits;        // bits of a sort key that may differ inside a segment (61, 64, or fewer)
   uint32_t cs_fix;     // largest mixed bucket the small-segment sort fixes by insertion
   uint32_t chain_spins;  // polls a chained scan waits for an earlier chunk before it gives up
   // Batch mode (Algorithm 2): the rows are nodes [ext_lo, ext_lo + n) of a

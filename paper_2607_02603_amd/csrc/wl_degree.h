@@ -44,7 +44,10 @@ __device__ __forceinline__ uint32_t degree_of(const Ctx& ctx, uint32_t i, bool r
 __global__ void __launch_bounds__(kBlock) k_deg_clear(Ctx ctx, DegScratch d, uint32_t maxd) {
   for (uint32_t x = blockIdx.x * kBlock + threadIdx.x; x <= maxd; x += gridDim.x * kBlock)
     d.dcount[x] = 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *d.nd = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *d.nd = 0;
+    clear_round_counters(ctx.st);
+  }
 }
 
 // The loops over the nodes below take kDegStep nodes per thread and step
@@ -170,16 +173,19 @@ __global__ void __launch_bounds__(kDegThreads) k_deg_ranks(Ctx ctx, DegScratch d
   // coincide: when w = 0 in F_p; in Z/2^64 when 2^64 divides (d - d') w,
   // which for degrees below 2^32 needs more than 32 trailing zero bits in w)
   {
-    uint32_t cnt_loc = 0, live_loc = 0;
+    uint32_t cnt_loc = 0, live_loc = 0, longest = 0;
+    unsigned long long ents = 0;
 #pragma unroll
     for (uint32_t u = 0; u < kPer; ++u) {
       const uint32_t t = t0 + u;
       if (t < D && (t == 0 || rk[t] != rk[t - 1])) {
         uint32_t size = 0;
         bool nonnull = false;
+        unsigned long long e = 0;
         uint32_t s = t;
         for (; s < D && rk[s] == rk[t]; ++s) {
           size += d.dcount[deg[s]];
+          e += (unsigned long long)d.dcount[deg[s]] * deg[s];
           nonnull = nonnull || deg[s] > 0;
         }
         d.rdeg[rk[t]] = s == t + 1 ? deg[t] : kDegMixed;
@@ -188,8 +194,14 @@ __global__ void __launch_bounds__(kDegThreads) k_deg_ranks(Ctx ctx, DegScratch d
         d.roff[rk[t]] = live ? size : 0u;
         cnt_loc += live ? size : 0u;
         live_loc += live ? 1u : 0u;
+        if (live) {
+          longest = max(longest, size);
+          ents += e;
+        }
       }
     }
+    if (ents) atomicAdd(&st->live_entries, ents);
+    if (longest > kSmallMax) atomicMax(&st->max_len2, longest);
     __syncthreads();
     const uint32_t inc = wave_incl_scan(cnt_loc);
     const uint32_t inc2 = wave_incl_scan(live_loc);

@@ -22,6 +22,7 @@
 #include <type_traits>
 #include <utility>
 #include <vector>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -240,6 +241,7 @@ bool wants_pb(const wl_csr* g) {
 Ctx make_ctx(const Layout& L, const wl_csr* g, uint8_t* ws, uint32_t* colors) {
   Ctx c{};
   c.ring = g_ring;
+  c.key_bits = g_ring ? 64 : 61;
   c.n = (uint32_t)L.n;
   c.nnz = L.nnz;
   c.rp32 = g->row_ptr32;
@@ -374,27 +376,25 @@ int check_graph(const wl_csr* g) {
   return WL_OK;
 }
 
-// Reads row_ptr[n] from the device and compares it with nnz.
-int check_nnz_device(const wl_csr* g, hipStream_t s) {
-  uint64_t last = 0;
-  if (g->row_ptr32) {
-    uint32_t v = 0;
-    HIP_TRY(hipMemcpyAsync(&v, g->row_ptr32 + g->n, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    last = v;
-  } else {
-    HIP_TRY(hipMemcpyAsync(&last, g->row_ptr64 + g->n, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-  }
-  if (last != g->nnz)
-    return fail(WL_EINVAL, "row_ptr[n] = %llu but nnz = %llu",
-                (unsigned long long)last, (unsigned long long)g->nnz);
-  return WL_OK;
+int fail_nnz(uint64_t nnz) {
+  return fail(WL_EINVAL, "row_ptr[n] does not equal nnz = %llu", (unsigned long long)nnz);
 }
 
 // ---------------------------------------------------------------------------
 // Device-side validation (WL_VALIDATE=1) and small set-up kernels.
 // ---------------------------------------------------------------------------
+
+// The device state of a call, from the kernel's argument (a copy from host
+// memory would have to be waited for before its source may go), and whether
+// row_ptr[n] is nnz (check_nnz): kErrNnz is read back with the call's first
+// counts, before any column is read.
+__global__ void k_state_init(Ctx ctx, DevState h, int check_nnz) {
+  if (check_nnz) {
+    const uint64_t last = ctx.rp64 ? ctx.rp64[ctx.n] : (uint64_t)ctx.rp32[ctx.n];
+    if (last != ctx.nnz) h.err = kErrNnz;
+  }
+  *ctx.st = h;
+}
 
 template <typename RP>
 __global__ void __launch_bounds__(kBlock) k_validate(Ctx ctx) {
@@ -426,14 +426,13 @@ __global__ void __launch_bounds__(kBlock) k_validate_sym(Ctx ctx) {
   atomicAdd(&ctx.st->sym_hash[1], b);
 }
 
-constexpr uint32_t kErrRowSum = 32u;  // DevState::err bit: a row sum above 2^32 (ring)
-
 // Theorem 1's precondition for Z/2^64: every row sum of A at most 2^32.  One
 // thread per row (its length, or the sum of at most 64 weights); the rows
 // with more weights are summed by all 64 lanes of the wave, one after the
 // other.  Sets kErrRowSum on a row above the bound.
 template <typename RP>
 __global__ void __launch_bounds__(kBlock) k_ring_rows(Ctx ctx) {
+  if (ctx.st->err & kErrNnz) return;
   const RP* rp = rowptr<RP>(ctx);
   const uint32_t lane = lane_id();
   const uint64_t lim = 1ull << 32;
@@ -498,11 +497,29 @@ __global__ void __launch_bounds__(kBlock) k_iota_zero(Ctx ctx) {
   }
 }
 
+__global__ void __launch_bounds__(kBlock) k_labels_max(Ctx ctx, const uint32_t* lab) {
+  uint32_t mx = 0;
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ctx.n; i += gridDim.x * kBlock)
+    mx = max(mx, lab[i]);
+  __shared__ uint32_t sm;
+  if (threadIdx.x == 0) sm = 0;
+  __syncthreads();
+  atomicMax(&sm, mx);
+  __syncthreads();
+  if (threadIdx.x == 0 && sm) atomicMax(&ctx.st->label_max, sm);
+}
+
+// Labels as sort keys: moved up until the largest one fills the key's top
+// bit, so that the first radix digit already separates them (label values
+// are small, and from bit 0 up every pass but the last found all digits
+// equal: four passes and read-backs where one does).
 __global__ void __launch_bounds__(kBlock) k_labels_to_z(Ctx ctx,
                                                         const uint32_t* lab) {
+  const uint32_t mx = ctx.st->label_max;
+  const int sh = ctx.key_bits - (mx ? 32 - __clz((int)mx) : 1);
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ctx.n;
        i += gridDim.x * kBlock)
-    ctx.z[i] = lab[i];
+    ctx.z[i] = (uint64_t)lab[i] << sh;
 }
 
 // Counting sort of the nodes by colour (colours < k): cstart, perm, act.
@@ -599,7 +616,7 @@ struct Session {
   // can be set for testing (WL_HOST_ROUNDS, WL_ASYNC_PASSES).
   uint32_t host_rounds_first = kHostRounds;
   int async_passes = kAsyncPassesDefault;
-  int passes_seen = 0;      // most radix passes a host-driven sort needed
+  int round_passes = 0;     // radix passes that the coming device-driven round launches
   // Live rounds alternate between two buffer sets: round r reads the set
   // (r - live_r0) & 1 and writes the other; ctx0 has set 0 current.
   Ctx ctx0{};
@@ -615,7 +632,6 @@ struct Session {
   // in every round it can serve (for testing).
   PbLayout P;
   PbCtx pb{};
-  uint32_t live_heavy = 0, live_mid = 0;  // blocks of k_spmv_mid
   bool live_mode = false;                  // incremental rounds (run_rsc)
   bool live_built = false;                 // live classes set up
   // The one-colour round by degree histogram (WL_DEGREE_ROUND=0 turns it off,
@@ -626,10 +642,11 @@ struct Session {
   // pos_deg holds the member-list positions of the coming round's live
   // classes (set by the one-colour round, cleared by the next image)
   bool deg_pos_fresh = false;
+  // host.live_entries holds the entries of the coming round's live rows
+  bool entries_fresh = false;
   bool sym_flag = false;
   int pb_mode = 1;
   DevState host;      // last copy of the device state
-  DevState init_src;  // source of the initial state copy
   uint32_t nscan;
   // diagnostics: SpMV launches bracketed by events, folded in at the next
   // read-back (a launch queued for a round that never ran is dropped)
@@ -733,7 +750,7 @@ struct Session {
       HIP_TRY(hipEventElapsedTime(&ms, call_ev[0], call_ev[1]));
       stats.call_ms = ms;
     }
-    if (int r = pull()) return r;
+    // the work counters are complete in the last read-back of the rounds
     stats.rounds = host.round;
     stats.gather.rows = host.work[kImgGather][0];
     stats.gather.entries = host.work[kImgGather][1];
@@ -751,11 +768,10 @@ struct Session {
     return stats_collect();
   }
 
-  // The source of the copy is a member that outlives it, and the copy is
-  // synchronised: an asynchronous copy from pageable host memory may read
-  // the source after this function returns.
+  // check_nnz: device graphs, whose row_ptr[n] the host has not seen
+  // (input_errors reports it after the next read-back).
   int init_state(uint64_t seed, uint32_t k, uint32_t round, uint32_t max_rounds,
-                 uint32_t dense) {
+                 uint32_t dense, bool check_nnz = false) {
     DevState h{};
     h.k = k;
     h.dense = dense;
@@ -763,15 +779,25 @@ struct Session {
     h.max_rounds = max_rounds;
     h.seed = seed;
     host = h;
-    init_src = h;
-    HIP_TRY(hipMemcpyAsync(ctx.st, &init_src, sizeof(DevState), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    hipLaunchKernelGGL(k_state_init, dim3(1), dim3(1), 0, s, ctx, h, check_nnz ? 1 : 0);
+    HIP_LAUNCH_CHECK();
+    return WL_OK;
+  }
+
+  // What the device found in the call's arguments before any column or
+  // weight was used; after a read-back.
+  int input_errors() const {
+    if (host.err & kErrNnz) return fail_nnz(L.nnz);
+    if (host.err & kErrRowSum)
+      return fail(WL_EOVERFLOW, "a row sum exceeds 2^32, the bound of arithmetic mod 2^64");
     return WL_OK;
   }
 
   int validate_device() {
     const char* v = getenv("WL_VALIDATE");
     if (!v || v[0] != '1') return WL_OK;
+    if (int r = pull()) return r;
+    if (int r = input_errors()) return r;
     uint32_t g = grid_for(std::max<uint64_t>(L.n, L.nnz));
     if (rp64)
       hipLaunchKernelGGL(k_validate<uint64_t>, dim3(g), dim3(kBlock), 0, s, ctx);
@@ -794,7 +820,8 @@ struct Session {
     return WL_OK;
   }
 
-  // In Z/2^64, Theorem 1's bound on the row sums (n < 2^32 holds already).
+  // In Z/2^64, Theorem 1's bound on the row sums (n < 2^32 holds already);
+  // input_errors reports it after the next read-back.
   int check_ring() {
     if (!ctx.ring) return WL_OK;
     const uint32_t g = grid_for(L.n, kBlock, 4096);
@@ -803,13 +830,7 @@ struct Session {
     else
       hipLaunchKernelGGL(k_ring_rows<uint32_t>, dim3(g), dim3(kBlock), 0, s, ctx);
     HIP_LAUNCH_CHECK();
-    if (int r = pull()) return r;
-    if (host.err & kErrRowSum) return fail_row_sum();
     return WL_OK;
-  }
-
-  static int fail_row_sum() {
-    return fail(WL_EOVERFLOW, "a row sum exceeds 2^32, the bound of arithmetic mod 2^64");
   }
 
   // The sorting networks (one launch: gt workgroups for the tiny segments,
@@ -825,7 +846,9 @@ struct Session {
       hipLaunchKernelGGL(k_sorts<false>, dim3(g), dim3(kBlock), 0, s, ctx, check_passes, gt, gp);
   }
 
-  // SpMV schedule (row bins and heavy chunks); once per call.
+  // SpMV schedule (row bins and heavy chunks); once per call.  heavy_only
+  // (the incremental rounds): the chunk count is not read back here, the next
+  // read-back brings it.
   int build_schedule(bool heavy_only = false) {
     const uint32_t nb = scan_blocks(L.n);
     if (rp64)
@@ -846,7 +869,9 @@ struct Session {
     }
     HIP_LAUNCH_CHECK();
     if (int r = pull()) return r;
+    if (int r = input_errors()) return r;
     const uint32_t nh = host.bin_cnt[3];
+    if (nh == 0) return WL_OK;
     const uint32_t hb = std::max<uint32_t>(1, std::min<uint32_t>(kScanBlocks, (nh + 255) / 256));
     if (rp64)
       hipLaunchKernelGGL(k_heavy_count<uint64_t>, dim3(hb), dim3(kBlock), 0, s, ctx);
@@ -858,7 +883,7 @@ struct Session {
     else
       hipLaunchKernelGGL(k_heavy_fill<uint32_t>, dim3(hb), dim3(kBlock), 0, s, ctx);
     HIP_LAUNCH_CHECK();
-    return pull();
+    return heavy_only ? WL_OK : pull();
   }
 
   template <typename RP, bool W, int M>
@@ -896,15 +921,21 @@ struct Session {
         pb_stop = true;
         return WL_OK;
       }
-      if (live_mode)
-        hipLaunchKernelGGL(k_live_count, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock), 0, s,
-                           ctx, 0);
-      else
-        hipLaunchKernelGGL(k_count_active<RP>, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock),
-                           0, s, ctx);
-      HIP_LAUNCH_CHECK();
-      if (int r = pull()) return r;
-      if (host.act_entries * 2 < L.nnz) {
+      uint64_t entries;
+      if (live_mode && entries_fresh) {
+        entries = host.live_entries;  // counted when the live classes were set up
+      } else {
+        if (live_mode)
+          hipLaunchKernelGGL(k_live_count, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock), 0, s,
+                             ctx, 0);
+        else
+          hipLaunchKernelGGL(k_count_active<RP>, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock),
+                             0, s, ctx);
+        HIP_LAUNCH_CHECK();
+        if (int r = pull()) return r;
+        entries = host.act_entries;
+      }
+      if (entries * 2 < L.nnz) {
         pb_stop = true;
         return WL_OK;
       }
@@ -1036,7 +1067,11 @@ struct Session {
     const uint32_t gl = live_grid();
     if (sflags & WL_STATS_WORK)
       hipLaunchKernelGGL(k_live_count, dim3(gl), dim3(kBlock), 0, s, ctx, 1);
-    const uint32_t mid = std::min(live_mid, grid_for(host.nl, kBlock / kWave, 2048));
+    // the static heavy chunks' blocks (all the layout holds while their number
+    // is not known), then waves for the rows queued per round
+    const uint32_t nch = host.bin_cnt[3] ? (host.n_chunks ? host.n_chunks : L.max_chunks) : 0;
+    const uint32_t live_heavy = nch ? grid_for(nch, kBlock / kWave) : 0;
+    const uint32_t mid = grid_for(host.nl, kBlock / kWave, 2048);
     const int long_rows = live_heavy || host.max_deg > kShortRow;
     timed_spmv(round, always, kImgGather, [&] {
       // node order (coalesced rows and colours) where the position map is kept:
@@ -1069,13 +1104,6 @@ struct Session {
       live_gather<true>(round, false);
     else
       live_gather<false>(round, false);
-  }
-
-  // Blocks of k_spmv_mid: the static heavy chunks, then waves for the rows
-  // queued per round.
-  void plan_live_grid() {
-    live_heavy = host.n_chunks ? grid_for(host.n_chunks, kBlock / kWave) : 0;
-    live_mid = grid_for(L.n, kBlock / kWave, 2048);
   }
 
   // Relabel by (c, z) for the current grouping; count_round = 0 for the
@@ -1114,7 +1142,6 @@ struct Session {
       HIP_LAUNCH_CHECK();
       if (int r = pull()) return r;
     }
-    if (pass > pass0) passes_seen = std::max(passes_seen, pass);
     sorts(host.n_tiny ? grid_for(host.n_tiny, kBlock / kWave, 8192) : 0,
           host.n_pico ? grid_for(host.n_pico, kBlock / 8, 8192) : 0,
           std::max<uint32_t>(host.n_msort ? grid_for(host.n_msort, kBlock / kWave, 8192) : 0,
@@ -1169,6 +1196,7 @@ struct Session {
   int build_live() {
     const uint32_t gn = grid_for(L.n, kBlock, 4096);
     const uint32_t k = host.k;
+    const uint32_t gb = grid_for(L.n, kBlock, 2048);
     DevState* st = ctx.st;
     hipLaunchKernelGGL(k_fill_u8, dim3(grid_for(k, kBlock, 4096)), dim3(kBlock), 0, s, ctx,
                        ctx.gnz, (uint64_t)k, (uint8_t)0);
@@ -1180,9 +1208,9 @@ struct Session {
                        ctx);
     xscan(nullptr, &st->k, ctx.gl, ctx.go, &st->n_live2, &st->nl2, nscan);
     if (rp64)
-      hipLaunchKernelGGL(k_live_build<uint64_t>, dim3(gn), dim3(kBlock), 0, s, ctx);
+      hipLaunchKernelGGL(k_live_build<uint64_t>, dim3(gb), dim3(kBlock), 0, s, ctx);
     else
-      hipLaunchKernelGGL(k_live_build<uint32_t>, dim3(gn), dim3(kBlock), 0, s, ctx);
+      hipLaunchKernelGGL(k_live_build<uint32_t>, dim3(gb), dim3(kBlock), 0, s, ctx);
     hipLaunchKernelGGL(k_live_commit, dim3(gn), dim3(kBlock), 0, s, ctx);
     hipLaunchKernelGGL(k_live_adopt, dim3(1), dim3(1), 0, s, ctx);
     HIP_LAUNCH_CHECK();
@@ -1242,7 +1270,7 @@ struct Session {
       hipLaunchKernelGGL(k_live_emit<uint64_t>, dim3(gl), dim3(kBlock), 0, s, ctx);
     else
       hipLaunchKernelGGL(k_live_emit<uint32_t>, dim3(gl), dim3(kBlock), 0, s, ctx);
-    hipLaunchKernelGGL(k_live_round_end, dim3(1), dim3(1), 0, s, ctx);
+    hipLaunchKernelGGL(k_live_round_end, dim3(1), dim3(1), 0, s, ctx, 0u);
   }
 
   // The one-colour round of an unweighted graph without a sort
@@ -1272,12 +1300,13 @@ struct Session {
     });
     hipLaunchKernelGGL(k_deg_list, dim3(gd), dim3(kBlock), 0, s, ctx, d, maxd);
     hipLaunchKernelGGL(k_deg_ranks, dim3(1), dim3(kDegThreads), 0, s, ctx, d);
-    HIP_LAUNCH_CHECK();
-    if (int r = pull()) return r;
-    if (host.deg_nd > kDegRanks) return WL_OK;
-    // the rank x block matrix of the placement lives in x (2n words): at
-    // most 1024 blocks, fewer when there are many ranks
-    const uint64_t K = std::max<uint32_t>(host.k_new, 1);
+    // The rest is launched without waiting for the number of ranks: with more
+    // degrees than k_deg_ranks takes, every kernel below returns at once.
+    // The rank x block matrix of the placement lives in x (2n words): at
+    // most 1024 blocks, fewer when there may be many ranks (D distinct
+    // degrees need 0 + 1 + ... + (D - 1) entries).
+    const uint64_t dmax = (uint64_t)std::sqrt(2.0 * (double)L.nnz) + 2;
+    const uint64_t K = std::min<uint64_t>({(uint64_t)maxd + 1, kDegRanks, dmax});
     const uint32_t nblk = (uint32_t)std::max<uint64_t>(
         1, std::min<uint64_t>({1024, grid_for(L.n, kBlock), 2 * L.n / K}));
     uint32_t* m = (uint32_t*)ctx.x;
@@ -1287,10 +1316,12 @@ struct Session {
     hipLaunchKernelGGL(k_deg_fill, dim3(grid_for((uint64_t)L.n / 4 + 1, kBlock, 1024)),
                        dim3(kBlock), 0, s, ctx, d);
     hipLaunchKernelGGL(k_deg_place<RP64>, dim3(nblk), dim3(kBlock), 0, s, ctx, d, m);
-    hipLaunchKernelGGL(k_live_round_end, dim3(1), dim3(1), 0, s, ctx);
+    hipLaunchKernelGGL(k_live_round_end, dim3(1), dim3(1), 0, s, ctx, kDegRanks);
     HIP_LAUNCH_CHECK();
     if (int r = pull()) return r;
+    if (host.deg_nd > kDegRanks) return WL_OK;
     *handled = true;
+    entries_fresh = true;
     deg_pos_fresh = ctx.pos_deg != nullptr && !host.done;
     return WL_OK;
   }
@@ -1319,19 +1350,21 @@ struct Session {
     if (int r = build_live()) return r;
     live_built = true;
     live_r0 = host.round;
-    hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(1), 0, s, ctx);
-    HIP_LAUNCH_CHECK();
+    entries_fresh = true;
     return WL_OK;
   }
 
-  // Live positions from which a host-driven round launches its first two
-  // radix passes before reading anything back.
-  static constexpr uint32_t kBlindPassesMin = 1u << 20;
-
+  // A round driven from the host: its launches are sized from the counts of
+  // the last read-back and go out at once, and one read-back ends it (each
+  // costs about 20 us, as much as five small kernels).  A round that needs
+  // more radix passes than it launched halts and is completed from there,
+  // its small sorts run again; from kBlindMax live positions on, where those
+  // sorts cost more than a read-back (R-MAT 27: 1.4 ms against 0.02), the
+  // passes are read back before the sorts instead.
+  static constexpr uint32_t kBlindMax = 1u << 17;
   int round_live() {
     if (degree_round_applies()) {
       ctx = ctx0;
-      hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(1), 0, s, ctx);
       bool handled = false;
       if (int r = rp64 ? degree_round<true>(&handled) : degree_round<false>(&handled)) return r;
       if (handled) {
@@ -1343,38 +1376,49 @@ struct Session {
     if (!live_built)
       if (int r = build_live_now()) return r;
     use_round_ctx(host.round);
-    hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(1), 0, s, ctx);
     if (int r = spmv_live()) return r;
+    entries_fresh = false;
     live_segments();
-    if (host.nl >= kBlindPassesMin) {
-      // a large live set: the first two radix passes go out without a
-      // read-back (a pass whose list is empty returns at once); the
-      // read-back after them sizes the small sorts and shows whether more
-      // passes are needed.  Pass 1 had work when pass 0 left big buckets.
-      radix_pass(0, 1024);
-      radix_pass(1, 1024);
-      HIP_LAUNCH_CHECK();
-      if (int r = pull()) return r;
-      passes_seen = std::max(passes_seen, big_entries(1) > 0 ? 2 : 1);
-      if (int r = finish_sort(2, false)) return r;
+    round_passes = any_big() ? std::max(async_passes, 1) : 0;
+    for (int pass = 0; pass < round_passes; ++pass) radix_pass(pass, 1024);
+    if (host.nl < kBlindMax || !round_passes) {
+      blind_sorts(round_passes);
     } else {
       HIP_LAUNCH_CHECK();
       if (int r = pull()) return r;
-      if (int r = finish_sort(0, false)) return r;
+      if (int r = finish_sort(round_passes, false)) return r;
     }
-    live_tail();
+    // the shift table can only be needed with that many classes
+    live_tail(host.n_live <= kShiftLds);
     HIP_LAUNCH_CHECK();
     if (int r = pull()) return r;
+    if (host.done == kHalted || host.done == kHaltedShift)
+      if (int r = finish_halted()) return r;
     if (host.err & kErrNotSymmetric)
       return fail(WL_EINVAL, "the graph is flagged symmetric but is not");
     if (host.err & kErrChain) return fail(WL_EHIP, "a chained scan did not complete");
     return WL_OK;
   }
 
-  // Radix passes launched per device-driven round: as many as the rounds so
-  // far needed (at least one), at most async_passes.
+  // Whether a live class may be longer than the one-workgroup sorts take
+  // (classes only shrink, so a count read back earlier is a bound).
+  bool any_big() const { return host.max_len > kSmallMax; }
+
+  // Radix passes launched per device-driven round: none when no class needs
+  // one, else as many as the rounds so far needed (at least one), at most
+  // async_passes.
   int async_pass_count() const {
-    return std::min(async_passes, std::max(1, passes_seen));
+    return any_big() ? std::min(async_passes, std::max(1, (int)host.npass)) : 0;
+  }
+
+  // The small sorts with nothing read back since the round began: workgroups
+  // for as many segments of each kind as nl positions can hold (without a
+  // radix pass the segments are the live classes).
+  void blind_sorts(int passes) {
+    const uint64_t nl = host.nl, m = passes ? nl : host.n_live;
+    sorts(grid_for(std::min<uint64_t>(m, nl / (kPicoMax + 1) + 1), kBlock / kWave, 8192),
+          grid_for(std::min<uint64_t>(m, nl / 2 + 1), kBlock / 8, 8192),
+          grid_for(std::min<uint64_t>(m, nl / (kTinyMax + 1) + 1), 1, 4096), passes);
   }
 
   // The same launched without reading anything back: grids are fixed for the
@@ -1386,7 +1430,7 @@ struct Session {
     use_round_ctx(round);
     spmv_live_async(round);
     live_segments();
-    const int ap = async_pass_count();
+    const int ap = round_passes;
     for (int pass = 0; pass < ap; ++pass) radix_pass(pass, 1024);
     // the small sorts' grids: enough blocks to fill the device, the segments
     // taken in grid-stride loops
@@ -1400,7 +1444,7 @@ struct Session {
   // grids are those of the capture; the live set only shrinks, so they stay
   // large enough.
   int ensure_graph(int p, uint32_t r) {
-    const int ap = async_pass_count();
+    const int ap = round_passes;
     if (gexec[p] && gexec_ap[p] == ap) return WL_OK;
     if (gexec[p]) {
       HIP_TRY(hipGraphExecDestroy(gexec[p]));
@@ -1433,6 +1477,7 @@ struct Session {
 
   // Queues rounds base .. base + count - 1 (count even) without a read-back.
   int launch_async_rounds(uint32_t base, uint32_t count) {
+    round_passes = async_pass_count();
     if (!use_graph) {
       for (uint32_t i = 0; i < count; ++i) round_live_async(base + i);
       HIP_LAUNCH_CHECK();
@@ -1460,11 +1505,18 @@ struct Session {
     if (why == kHaltedShift) {
       live_shift_end(true);
     } else {
-      if (int r = finish_sort(async_pass_count(), false)) return r;
+      if (int r = finish_sort(round_passes, false)) return r;
       live_tail();
     }
     HIP_LAUNCH_CHECK();
     return pull();
+  }
+
+  void labels_to_keys(const uint32_t* lab) {
+    hipLaunchKernelGGL(k_labels_max, dim3(grid_for(L.n, 4 * kBlock, 256)), dim3(kBlock), 0, s, ctx,
+                       lab);
+    hipLaunchKernelGGL(k_labels_to_z, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock), 0, s, ctx,
+                       lab);
   }
 
   // Algorithm 1 to completion on the session's graph, from labels on the
@@ -1474,8 +1526,7 @@ struct Session {
     hipLaunchKernelGGL(k_iota_zero, dim3(gn), dim3(kBlock), 0, s, ctx);
     HIP_LAUNCH_CHECK();
     if (init_dev) {
-      hipLaunchKernelGGL(k_labels_to_z, dim3(gn), dim3(kBlock), 0, s, ctx, init_dev);
-      HIP_LAUNCH_CHECK();
+      labels_to_keys(init_dev);
       if (int r = relabel(0)) return r;
     }
     if (int r = build_schedule(true)) return r;
@@ -1490,7 +1541,6 @@ struct Session {
     if (!degree_round_applies())
       if (int r = build_live_now()) return r;
     live_mode = true;
-    plan_live_grid();
     // The first rounds are driven from the host (each reads its counts
     // back); after that, rounds go to the device in groups of 'ahead' with
     // one read-back per group.  Rounds queued past the last one find the
@@ -1550,9 +1600,7 @@ struct Session {
     }
     HIP_LAUNCH_CHECK();
     if (int r = pull()) return r;
-    if (host.err == kErrSmallNnz)
-      return fail(WL_EINVAL, "row_ptr[n] does not equal nnz = %llu", (unsigned long long)L.nnz);
-    if (host.err == kErrSmallRow) return fail_row_sum();
+    if (int r = input_errors()) return r;
     if (diag) {
       stats = wl_stats{};
       stats.rounds = host.round;
@@ -1634,14 +1682,10 @@ int run_in_core(Session& S, const wl_csr* g, const uint32_t* init, uint64_t seed
   const uint32_t cap =
       max_rounds ? max_rounds : (uint32_t)std::min<uint64_t>(g->n + 1, 0xFFFFFFFFull);
   if (S.small_applies(diag)) return S.run_small(init, seed, cap, diag);
-  if (int r = check_nnz_device(g, S.s)) return r;
-  if (int r = S.init_state(seed, 1, 0, cap, 1)) return r;
+  if (int r = S.init_state(seed, 1, 0, cap, 1, true)) return r;
   if (int r = S.validate_device()) return r;
   if (int r = S.check_ring()) return r;
-  if (!diag) {
-    if (int r = S.run_rsc(init)) return r;
-    return S.pull();
-  }
+  if (!diag) return S.run_rsc(init);
   if (int r = S.stats_begin()) return r;
   if (int r = S.run_rsc(init)) return r;
   return S.stats_end();
@@ -1697,10 +1741,12 @@ int verify_run(const wl_csr* g, const uint32_t* color, uint32_t k, uint8_t* ws,
     return WL_OK;
   };
   const uint32_t gn = grid_for(v.n, kBlock, 4096);
-  hipLaunchKernelGGL(k_v_clear<K>, dim3(grid_for(k, kBlock, 4096)), dim3(kBlock), 0, s, v);
+  hipLaunchKernelGGL(k_v_clear<K>, dim3(grid_for(k, kBlock, 4096)), dim3(kBlock), 0, s, v,
+                     g->nnz);
   hipLaunchKernelGGL(k_v_rep<K>, dim3(gn), dim3(kBlock), 0, s, v);
   HIP_LAUNCH_CHECK();
   if (int r = pull()) return r;
+  if (h.err & kVErrNnz) return fail_nnz(g->nnz);
   if (h.err & kVErrColor) return fail(WL_EINVAL, "a colour is >= k");
   hipLaunchKernelGGL(k_v_multi<K>, dim3(gn), dim3(kBlock), 0, s, v);
   hipLaunchKernelGGL(k_v_bin<K>, dim3(gn), dim3(kBlock), 0, s, v);
@@ -1840,8 +1886,7 @@ int wl_refine_round(const wl_csr* g, const uint32_t* color_in, uint32_t k_in,
     return fail(WL_EINVAL, "k_in = %u must be in [1, n]", k_in);
   Session S;
   if (int r = open_session(S, g, color_out, workspace, ws_bytes, stream)) return r;
-  if (int r = check_nnz_device(g, S.s)) return r;
-  if (int r = S.init_state(seed, k_in, round, round + 1, 0)) return r;
+  if (int r = S.init_state(seed, k_in, round, round + 1, 0, true)) return r;
   if (int r = S.validate_device()) return r;
   if (int r = S.check_ring()) return r;
   const uint32_t gn = grid_for(g->n, kBlock, 4096);
@@ -1849,6 +1894,7 @@ int wl_refine_round(const wl_csr* g, const uint32_t* color_in, uint32_t k_in,
                      k_in);
   HIP_LAUNCH_CHECK();
   if (int r = S.pull()) return r;
+  if (int r = S.input_errors()) return r;
   if (S.host.err & 4u) return fail(WL_EINVAL, "a colour is >= k_in");
   if (color_out != color_in)
     HIP_TRY(hipMemcpyAsync(color_out, color_in, 4 * g->n, hipMemcpyDeviceToDevice, S.s));
@@ -2054,7 +2100,6 @@ int wl_verify_stable(const wl_csr* g, const uint32_t* color, uint32_t k,
     return fail(WL_EBUDGET, "workspace has %llu bytes, %llu needed",
                 (unsigned long long)ws_bytes, (unsigned long long)L.total);
   hipStream_t s = (hipStream_t)stream;
-  if (int r = check_nnz_device(g, s)) return r;
   if (g->weight)
     return verify_run<uint64_t>(g, color, k, (uint8_t*)workspace, L, s);
   return verify_run<uint32_t>(g, color, k, (uint8_t*)workspace, L, s);

@@ -193,10 +193,13 @@ __global__ void __launch_bounds__(kBlock) k_live_class_vals(Ctx ctx) {
 }
 
 // Members of the live classes in colour order, with their row spans (into
-// the '2' buffers, made current by k_live_commit).
+// the '2' buffers, made current by k_live_commit); their entries are summed
+// in live_entries and their largest size taken in max_len2.
 template <typename RP>
 __global__ void __launch_bounds__(kBlock) k_live_build(Ctx ctx) {
   const RP* rp = rowptr<RP>(ctx);
+  unsigned long long ents = 0;
+  uint32_t longest = 0;
   for (uint32_t p = blockIdx.x * kBlock + threadIdx.x; p < ctx.n; p += gridDim.x * kBlock) {
     const uint32_t b = ctx.ids[p], v = ctx.perm[p];
     const bool live = class_live(ctx, b);
@@ -212,11 +215,33 @@ __global__ void __launch_bounds__(kBlock) k_live_build(Ctx ctx) {
     ctx.qcls2[q] = j;
     ctx.rs2[q] = r0;
     ctx.rl2[q] = (uint32_t)(r1 - r0);
+    ents += r1 - r0;
     if (p == s) {
       ctx.lcold2[j] = b;
       ctx.loff2[j] = ctx.go[b];
       ctx.llen2[j] = ctx.cstart[b + 1] - s;
+      longest = max(longest, ctx.cstart[b + 1] - s);
     }
+  }
+  // one atomic per workgroup (one per wave cost 0.19 ms on 4e6 nodes)
+  __shared__ unsigned long long se[kBlock / kWave];
+  __shared__ uint32_t sl[kBlock / kWave];
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    ents += __shfl_xor(ents, off, kWave);
+    longest = max(longest, (uint32_t)__shfl_xor(longest, off, kWave));
+  }
+  if (lane_id() == 0) {
+    se[threadIdx.x / kWave] = ents;
+    sl[threadIdx.x / kWave] = longest;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kBlock / kWave; ++w) {
+      ents += se[w];
+      longest = max(longest, sl[w]);
+    }
+    if (ents) atomicAdd(&ctx.st->live_entries, ents);
+    if (longest > kSmallMax) atomicMax(&ctx.st->max_len2, longest);
   }
 }
 
@@ -380,7 +405,7 @@ __global__ void __launch_bounds__(kBlock) k_live_subs_splits(Ctx ctx, uint32_t n
   if (blockIdx.x < nscan) {
     uint32_t lo, hi;
     xscan_range(ns, blockIdx.x, nscan, &lo, &hi);
-    uint32_t sa = 0, sb = 0;
+    uint32_t sa = 0, sb = 0, longest = 0;
     for (uint32_t g0 = lo + kScanItems * threadIdx.x; g0 < hi; g0 += kScanStep) {
 #pragma unroll
       for (uint32_t u = 0; u < kScanItems; ++u) {
@@ -398,8 +423,12 @@ __global__ void __launch_bounds__(kBlock) k_live_subs_splits(Ctx ctx, uint32_t n
         ctx.go[g] = live ? len : 0u;
         sa += live ? 1u : 0u;
         sb += live ? len : 0u;
+        longest = max(longest, live ? len : 0u);
       }
     }
+    // classes beyond the one-workgroup sorts are what the host asks about;
+    // with none the maximum stays 0 and costs no atomic
+    if (longest > kSmallMax) atomicMax(&st->max_len2, longest);
     uint32_t ta, tb;
     block_excl_scan(sa, sh, &ta);
     block_excl_scan(sb, sh, &tb);
@@ -660,14 +689,18 @@ __global__ void k_live_adopt(Ctx ctx) {
   DevState* st = ctx.st;
   st->n_live = st->n_live2;
   st->nl = st->nl2;
+  const uint32_t longest = st->max_len2;
+  clear_round_counters(st);
+  st->max_len = longest;
 }
 
 // End of a live round (one thread): the colour count, round counter,
 // termination and new live counts; the per-round counters are cleared.  No
-// argument depends on the round, so the launch can be replayed.
-__global__ void k_live_round_end(Ctx ctx) {
+// argument depends on the round, so the launch can be replayed.  degree: ends
+// the one-colour round, unless its ranking had to give up.
+__global__ void k_live_round_end(Ctx ctx, uint32_t degree_ranks) {
   DevState* st = ctx.st;
-  if (st->done) return;
+  if (st->done || (degree_ranks && st->deg_nd > degree_ranks)) return;
   const uint32_t kn = st->k_new;
   st->round += 1;
   if (st->nosplit) {
@@ -676,19 +709,10 @@ __global__ void k_live_round_end(Ctx ctx) {
     if (st->round >= st->max_rounds) st->done = 2;
     st->n_live = st->n_live2;
     st->nl = st->nl2;
+    st->max_len = st->max_len2;
   }
   st->k = kn;
-  st->n_small = 0;
-  st->n_tiny = 0;
-  st->n_pico = 0;
-  st->n_msort = 0;
-  st->big[0] = 0;
-  st->big[1] = 0;
-  for (int i = 0; i < 4; ++i) st->tickets[i] = 0;
-  st->act_entries = 0;
-  st->n_split = 0;
-  st->n_mid = 0;
-  st->n_hlive = 0;
+  clear_round_counters(st);
 }
 
 }  // namespace wl

@@ -500,7 +500,7 @@ int streamed_run(const HostGraph& G, const uint32_t* labels, uint64_t seed,
   if (labels) {
     uint32_t* lab_dev = (uint32_t*)S.ctx.x;
     if (int r = hc.h2d(lab_dev, labels, 4 * n)) return r;
-    hipLaunchKernelGGL(k_labels_to_z, dim3(gn), dim3(kBlock), 0, s, S.ctx, lab_dev);
+    S.labels_to_keys(lab_dev);
     HIP_LAUNCH_CHECK();
     if (int r = S.relabel(0)) return r;
   }
@@ -1151,6 +1151,7 @@ int batched_run(const wl_csr* g, const uint32_t* init_host, uint64_t seed,
             if (int r = open_session(S, &sg, nullptr, W + QL.core, QL.total - QL.core, s))
               return r;
             S.ctx.keys_mat = 1;
+            S.ctx.key_bits = kQShift;  // a segment is one row's: equal above the target
             if (int r = S.init_state(0, 1, 0, 1, 1)) return r;
             hipLaunchKernelGGL(k_q_keys, dim3(grid_for(len, kBlock, 8192)), dim3(kBlock), 0, s,
                                S.ctx, D.rp, D.col, G.wt ? D.wt : nullptr, blk_dev, isrep_dev,
@@ -1190,6 +1191,7 @@ int batched_run(const wl_csr* g, const uint32_t* init_host, uint64_t seed,
         if (int r = open_session(S, &sg, nullptr, W + QL.core, QL.total - QL.core, s))
           return r;
         S.ctx.keys_mat = 1;
+        S.ctx.key_bits = kQShift;  // a segment is one row's: equal above the target
         if (int r = S.init_state(0, 1, 0, 1, 1)) return r;
         hipLaunchKernelGGL(k_q_keys, dim3(grid_for(ent, kBlock, 8192)),
                            dim3(kBlock), 0, s, S.ctx, D.rp, D.col,

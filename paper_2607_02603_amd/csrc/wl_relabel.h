@@ -28,17 +28,16 @@ namespace wl {
 constexpr uint32_t kHalted = 3;
 constexpr uint32_t kHaltedShift = 4;
 
-// Digit of a radix pass: 8-bit digits from the top of the key (61-bit
-// residues of F_p, or 64-bit values of Z/2^64), the last one shorter for F_p.
-__device__ __forceinline__ uint32_t digit_of(uint64_t key, int pass, uint32_t ring) {
-  const int hi = (ring ? 64 : 61) - kRadixBits * pass;
+// Digit of a radix pass: 8-bit digits from the top of the key's 'bits' bits
+// (61-bit residues of F_p, 64-bit values of Z/2^64, the 30 bits of the target
+// block in a quotient row), the last one shorter unless 8 divides them.
+__device__ __forceinline__ uint32_t digit_of(uint64_t key, int pass, int bits) {
+  const int hi = max(bits - kRadixBits * pass, 0);
   const int lo = hi > kRadixBits ? hi - kRadixBits : 0;
   return (uint32_t)((key >> lo) & ((1ull << (hi - lo)) - 1));
 }
 
-__global__ void k_round_begin(Ctx ctx) {
-  DevState* st = ctx.st;
-  if (st->done) return;
+__device__ __forceinline__ void clear_round_counters(DevState* st) {
   st->n_small = 0;
   st->n_tiny = 0;
   st->n_pico = 0;
@@ -50,6 +49,12 @@ __global__ void k_round_begin(Ctx ctx) {
   st->n_split = 0;
   st->n_mid = 0;
   st->n_hlive = 0;
+  st->max_len2 = 0;
+}
+
+__global__ void k_round_begin(Ctx ctx) {
+  if (ctx.st->done) return;
+  clear_round_counters(ctx.st);
 }
 
 __global__ void __launch_bounds__(kBlock) k_fill_u8(Ctx ctx, uint8_t* p,
@@ -202,6 +207,7 @@ __global__ void __launch_bounds__(kBlock) k_big_hist(Ctx ctx, int pass) {
   if (blockIdx.x == 0 && threadIdx.x == 0) st->big[cur ^ 1] = 0;
   const uint32_t nb = big_count(st, cur), nt = big_tiles(st, cur);
   if (nb == 0) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->npass = max(st->npass, (uint32_t)pass + 1);
   __shared__ uint32_t cnt[kRadix];
   __shared__ unsigned long long mn[kRadix], mx[kRadix];
   for (uint32_t i = blockIdx.x; i < nt; i += gridDim.x) {
@@ -226,7 +232,7 @@ __global__ void __launch_bounds__(kBlock) k_big_hist(Ctx ctx, int pass) {
     for (uint32_t q = 0; q < kTilePerThread; ++q) {
       if (r.beg + q * kBlock + threadIdx.x >= r.end) break;
       const uint64_t key = kv[q];
-      const uint32_t d = digit_of(key, pass, ctx.ring);
+      const uint32_t d = digit_of(key, pass, ctx.key_bits);
       if (d != rd) {
         if (rc) {
           atomicAdd(&cnt[rd], rc);
@@ -338,7 +344,7 @@ __global__ void __launch_bounds__(kBlock) k_big_scatter(Ctx ctx, int pass) {
       const uint32_t p = r.beg + q * kBlock + threadIdx.x;
       if (p < r.end) {
         kv[q] = ctx.keys[p];
-        dg[q] = digit_of(kv[q], pass, ctx.ring);
+        dg[q] = digit_of(kv[q], pass, ctx.key_bits);
         slot[q] = atomicAdd(&lcnt[dg[q]], 1u);
       }
     }

@@ -40,8 +40,6 @@ constexpr uint32_t kSmallLane = 32;           // longest row of one thread
 constexpr uint32_t kSmallHalf = 512;          // ... of 16 lanes
 constexpr uint32_t kSmallRank = 32;           // longest segment ranked by pairs
 constexpr uint8_t kSmallMixed = 0x80;         // used[]: the segment's keys differ
-constexpr uint32_t kErrSmallNnz = 128u;       // DevState::err bit: row_ptr[n] != nnz
-constexpr uint32_t kErrSmallRow = 256u;       // ... a row sum above 2^32 (ring)
 
 struct SmallArgs {
   const uint32_t* init;  // labels, or NULL
@@ -238,7 +236,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(Ctx ctx, SmallArgs A) {
   auto rp_in = [&](uint32_t i) -> uint64_t { return RP64 ? ctx.rp64[i] : (uint64_t)ctx.rp32[i]; };
   if (rp_in(n) != ctx.nnz) {
     if (threadIdx.x == 0) {
-      st->err = kErrSmallNnz;
+      st->err = kErrNnz;
       st->done = 1;
     }
     return;
@@ -269,7 +267,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(Ctx ctx, SmallArgs A) {
     __syncthreads();
     if (L.bad) {
       if (threadIdx.x == 0) {
-        st->err = kErrSmallRow;
+        st->err = kErrRowSum;
         st->done = 1;
       }
       return;

@@ -31,6 +31,7 @@ namespace wl {
 constexpr uint32_t kVChunk = 4096;
 constexpr uint32_t kVErrColor = 1u;     // a colour >= k
 constexpr uint32_t kVErrMismatch = 2u;  // two nodes of one class differ
+constexpr uint32_t kVErrNnz = 4u;       // row_ptr[n] is not nnz
 
 struct VerState {
   uint32_t err;
@@ -83,13 +84,13 @@ __device__ __forceinline__ uint64_t v_key<uint64_t>(const VerCtx<uint64_t>& v, u
 }
 
 template <typename K>
-__global__ void __launch_bounds__(kBlock) k_v_clear(VerCtx<K> v) {
+__global__ void __launch_bounds__(kBlock) k_v_clear(VerCtx<K> v, uint64_t nnz) {
   for (uint32_t b = blockIdx.x * kBlock + threadIdx.x; b < v.k; b += gridDim.x * kBlock) {
     v.rep[b] = 0xFFFFFFFFu;
     v.multi[b] = 0;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    v.st->err = 0;
+    v.st->err = v_beg(v, v.n) == nnz ? 0u : kVErrNnz;
     v.st->n_mid = 0;
     v.st->n_hub = 0;
     v.st->n_hub_chunks = 0;

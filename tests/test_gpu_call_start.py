@@ -1,0 +1,53 @@
+"""The start of an in-core call on the general path (graphs beyond the
+one-workgroup one): labels of every magnitude become the canonical initial
+colours, and a row pointer that does not end at nnz is refused by every
+in-core entry point before any column is read."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2607_02603_amd as wl
+from paper_2607_02603_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("top", [0, 1, 4, 255, 256, 65537, 2**31, 2**32 - 1])
+@pytest.mark.parametrize("ring", [False, True])
+def test_labels(top, ring):
+    g = inputs.er_graph(9001, 20000, seed=3)
+    rng = np.random.default_rng(top % 1000)
+    # few and many distinct labels, the largest among them
+    lab = rng.integers(0, top + 1, g.n, dtype=np.uint64).astype(np.uint32)
+    lab[rng.random(g.n) < 0.5] = 0
+    lab[17] = top
+    ref, kr, rr, _, st = oracle.stable_coloring(g.row_ptr, g.col, None, lab, 5,
+                                                q=64 if ring else 0)
+    assert st == 0
+    dg = wl.Graph.from_numpy(g.n, g.row_ptr, g.col, device="cuda")
+    print(f"labels up to {top} ring={ring}", flush=True)
+    with wl.precision(wl.WL_PRECISION_RING64 if ring else wl.WL_PRECISION_FP):
+        c, k, r = wl.wl_stable_coloring(dg, torch.from_numpy(lab.view(np.int32)).cuda(), 5)
+    assert (k, r) == (kr, rr)
+    assert np.array_equal(c.cpu().numpy().view(np.uint32), ref)
+
+
+@pytest.mark.parametrize("n", [900, 9001])
+@pytest.mark.parametrize("ring", [False, True])
+def test_row_pointer_that_does_not_end_at_nnz(n, ring):
+    g = inputs.er_graph(n, 2 * n, seed=1)
+    col = np.concatenate([g.col, g.col[:5]])
+    wt = np.ones(col.size, np.uint32)
+    color = torch.zeros(n, dtype=torch.int32, device="cuda")
+    for w in (None, wt):
+        dg = wl.Graph.from_numpy(n, g.row_ptr, col, w, device="cuda")
+        with wl.precision(wl.WL_PRECISION_RING64 if ring else wl.WL_PRECISION_FP):
+            for call in (lambda: wl.wl_stable_coloring(dg),
+                         lambda: wl.wl_stable_coloring(dg, color),
+                         lambda: wl.wl_stable_coloring_noalloc(dg),
+                         lambda: wl.wl_refine_round(dg, color, 1, 0, 0),
+                         lambda: wl.wl_verify_stable(dg, color, 1)):
+                with pytest.raises(wl.WlError) as e:
+                    call()
+                assert e.value.code == wl.WL_EINVAL
