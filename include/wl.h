@@ -319,9 +319,10 @@ const char *wl_last_error(void);
  * The image of a round is one of three kinds: 'gather' (a row reads its
  * neighbours' values), 'pb' (propagation blocking on a symmetric graph: its
  * passes count as one launch) or 'uniform' (rounds with a single colour).
- * With WL_GRAPH=1 in the environment, the rounds that run without a
- * read-back are replayed from a HIP graph: their image launches are counted
- * but not timed, so 'ms' then covers the host-driven rounds only.
+ * Frontier rounds (see WL_FRONT), and with WL_GRAPH=1 in the environment the
+ * rounds that are replayed from a HIP graph, have their image launches counted
+ * but not timed, so 'ms' covers the other rounds only; with WL_STATS_WORK no
+ * frontier rounds are run.
  * wl_stats_get() returns the figures of the last in-core call on this thread.
  * Both return WL_OK, or WL_EINVAL for a NULL pointer / unknown flag. */
 #define WL_STATS_TIME 1
@@ -351,6 +352,10 @@ int wl_stats_get(wl_stats *out);
  *                        (default: on when at least half the entries feed
  *                        rows whose image is needed).
  *   WL_DEGREE_ROUND=0    no histogram round from one colour.
+ *   WL_FRONT=n           symmetric graphs of short rows: frontier rounds, whose
+ *                        cost follows what changes, tried from round n on
+ *                        (default 12; 0 never, the default while
+ *                        WL_HOST_ROUNDS, WL_ASYNC_PASSES or WL_GRAPH is set).
  *   WL_SMALL=0           graphs of at most 4096 nodes and 2^17 entries take
  *                        the general path too, not the one-workgroup one (as
  *                        they do while WL_VALIDATE or a tuning variable of

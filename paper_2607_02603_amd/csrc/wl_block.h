@@ -230,6 +230,12 @@ __device__ __forceinline__ uint64_t read_lane64(uint64_t v, int l) {
          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
 }
 
+// Lane of the r-th set bit of m (r from 0; 64 when there are fewer).
+__device__ __forceinline__ int nth_bit(unsigned long long m, int r) {
+  for (; r > 0 && m; --r) m &= m - 1;
+  return m ? __builtin_ctzll(m) : kWave;
+}
+
 // Lanes of the wave that are active and hold the same key as this lane
 // (0 for an inactive lane); one pass per distinct key among the active
 // lanes.  Every lane of the calling control flow must call it.

@@ -38,6 +38,7 @@
 #include "wl_spmv.h"
 #include "wl_push.h"
 #include "wl_small.h"
+#include "wl_front.h"
 #include "wl_quotient.h"
 #include "wl_verify.h"
 
@@ -593,12 +594,20 @@ __global__ void __launch_bounds__(kBlock) k_place_colors(Ctx ctx) {
     ctx.act[i] = ctx.cstart[c + 1] - s >= 2 ? 1 : 0;
   }
 }
+// Colour of every position (after k_place_colors; ids is no counter any more).
+__global__ void __launch_bounds__(kBlock) k_position_colors(Ctx ctx) {
+  for (uint32_t p = blockIdx.x * kBlock + threadIdx.x; p < ctx.n; p += gridDim.x * kBlock)
+    ctx.ids[p] = ctx.c[ctx.perm[p]];
+}
 
 // ---------------------------------------------------------------------------
 // One call's device session.
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t kHostRounds = 8;
+// Rounds before frontier rounds are tried: most graphs are stable by then, and
+// the change costs about as much as two full rounds.
+constexpr uint32_t kFrontFrom = 12;
 constexpr int kAsyncPassesDefault = 2;
 
 int env_int(const char* name, int lo, int hi, int dflt) {
@@ -670,6 +679,8 @@ struct Session {
   // stream.
   bool use_graph = false;
   bool capturing = false;
+  // Frontier rounds (wl_front.h): tried from this round on (0: never).
+  uint32_t front_from = 0;
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   int gexec_ap[2] = {-1, -1};  // radix passes per round when captured
@@ -1519,6 +1530,126 @@ struct Session {
                        lab);
   }
 
+  // Nodes grouped by their colours (colours < k): cstart and perm.  Reads
+  // the colour count k from the device state.
+  void group_by_color(uint32_t k) {
+    const uint32_t gn = grid_for(L.n, kBlock, 4096);
+    hipLaunchKernelGGL(k_count_colors, dim3(grid_for(k + 1ull, kBlock, 4096)), dim3(kBlock), 0, s,
+                       ctx, k);
+    hipLaunchKernelGGL(k_hist_colors, dim3(grid_for(L.n, kColorTile, 4096)), dim3(kBlock), 0, s,
+                       ctx);
+    // the class starts by the device-wide scan over the k sizes
+    xscan(nullptr, &ctx.st->k, ctx.ids, nullptr, nullptr, nullptr, scan_blocks(k));
+    hipLaunchKernelGGL(k_starts_colors, dim3(grid_for(k + 1ull, kBlock, 4096)), dim3(kBlock), 0,
+                       s, ctx, k);
+    hipLaunchKernelGGL(k_place_colors, dim3(gn), dim3(kBlock), 0, s, ctx);
+  }
+
+  // ---- frontier rounds (wl_front.h) ----
+
+  // Whether the graph's rounds may become frontier rounds: marks travel over
+  // the rows, so A must be its own transpose; rows are walked by few lanes,
+  // so they are short.  In Z/2^64 a difference of counts whose entries share
+  // a factor 2^v vanishes with probability 2^-(64 - v), so there only counts
+  // of at most kShortRow = 2^4 (unweighted rows of that length) qualify.
+  bool front_applies() const {
+    return front_from != 0 && sym_flag && !ctx.batch && L.n < kFrontSingle &&
+           host.max_deg <= kFrontDeg && !(sflags & WL_STATS_WORK) &&
+           (!ctx.ring || (!weighted && host.max_deg <= kShortRow));
+  }
+
+  // Its arrays lie over the live-class state, which is rebuilt afterwards.
+  FrontCtx front_ctx() const {
+    const Ctx& c = ctx0;
+    const uint64_t n = L.n;
+    FrontCtx F{};
+    F.r = (FrontRound*)c.flags;
+    F.cls = c.c;
+    F.mem = c.perm;
+    F.posn = (uint32_t*)c.x;
+    F.stamp = F.posn + n;
+    F.tnode = (uint32_t*)c.z;
+    F.tc = F.tnode + n;
+    F.start = (uint32_t*)c.keys;
+    F.size = F.start + n;
+    F.color = (uint32_t*)c.keys_tmp;
+    F.ord[0] = F.color + n;
+    F.ord[1] = (uint32_t*)c.rs;
+    F.ex = F.ord[1] + n;
+    F.tkey = (unsigned long long*)c.rs2;
+    F.best = F.tkey;  // at the entry only
+    F.exbase = c.lcold;    // 1.5 n words each
+    F.bsum = c.lcold + n;
+    F.exret = c.lcold2;
+    F.S[0] = c.rl;
+    F.S[1] = c.rl2;
+    F.scls = c.qcls2;
+    F.hole = c.perm_tmp;
+    F.mover = c.cstart;
+    F.dirty = c.ids;
+    F.prev = c.rows;  // no row is longer than kHeavyChunk: the list is empty
+    return F;
+  }
+
+  template <bool RP64, bool W>
+  void front_round(const FrontCtx& F, uint32_t i, uint32_t lg) {
+    hipLaunchKernelGGL((k_front_touch<RP64, W>),
+                       dim3(grid_for((uint64_t)L.n << lg, 8 * kBlock, 512)), dim3(kBlock), 0, s,
+                       ctx, F, i, lg);
+    hipLaunchKernelGGL((k_front_split<RP64, W>), dim3(kFrontBig + grid_for(L.n, kBlock, 240)),
+                       dim3(kSmallThreads), 0, s, ctx, F, i);
+    hipLaunchKernelGGL(k_front_apply, dim3(grid_for(L.n, kFrontChunk, 256)), dim3(kBlock), 0, s,
+                       ctx, F, i);
+  }
+
+  // Runs frontier rounds after the full round that just ended, whose start
+  // colours are in F.prev, and returns to the full rounds' state.  *again:
+  // the coming full round only confirms that no class splits.
+  int front_rounds(bool* again, bool* ran) {
+    *again = false;
+    *ran = false;
+    ctx = ctx0;
+    const FrontCtx F = front_ctx();
+    const uint32_t gn = grid_for(L.n, kBlock, 4096);
+    group_by_color(host.k);
+    hipLaunchKernelGGL(k_front_begin, dim3(1), dim3(1), 0, s, ctx, F);
+    hipLaunchKernelGGL(k_front_classes, dim3(gn), dim3(kBlock), 0, s, ctx, F);
+    hipLaunchKernelGGL(k_front_best, dim3(gn), dim3(kBlock), 0, s, ctx, F);
+    hipLaunchKernelGGL(k_front_seed, dim3(gn), dim3(kBlock), 0, s, ctx, F);
+    HIP_LAUNCH_CHECK();
+    FrontRound fr{};
+    HIP_TRY(hipMemcpyAsync(&fr, F.r, sizeof fr, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    const uint32_t lg = host.max_deg <= 4 ? 2 : (host.max_deg <= 8 ? 3 : 4);
+    const uint32_t round0 = fr.round;
+    uint32_t i = 0, ahead = 8;
+    // with a quarter of the nodes in S a full round is no dearer
+    while ((uint64_t)fr.ns * 4 <= L.n && !fr.done) {
+      for (uint32_t x = 0; x < ahead; ++x, ++i) {
+        if (rp64) {
+          if (weighted) front_round<true, true>(F, i, lg); else front_round<true, false>(F, i, lg);
+        } else {
+          if (weighted) front_round<false, true>(F, i, lg);
+          else front_round<false, false>(F, i, lg);
+        }
+      }
+      HIP_LAUNCH_CHECK();
+      HIP_TRY(hipMemcpyAsync(&fr, F.r + (i & 3), sizeof fr, hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      ahead = std::min<uint32_t>(2 * ahead, 64);
+    }
+    *again = fr.done == kFrontStable;
+    *ran = fr.round > round0;
+    if (sflags & WL_STATS_TIME) stats.gather.launches += fr.round - round0;  // not timed
+    hipLaunchKernelGGL(k_front_exit, dim3(gn), dim3(kBlock), 0, s, ctx, F, i);
+    HIP_LAUNCH_CHECK();
+    if (fr.done == 2) return pull();
+    group_by_color(fr.k);
+    hipLaunchKernelGGL(k_position_colors, dim3(gn), dim3(kBlock), 0, s, ctx);
+    host.k = fr.k;
+    return build_live_now();
+  }
+
   // Algorithm 1 to completion on the session's graph, from labels on the
   // device (or the trivial partition).  Leaves colours in ctx.c.
   int run_rsc(const uint32_t* init_dev) {
@@ -1546,7 +1677,26 @@ struct Session {
     // one read-back per group.  Rounds queued past the last one find the
     // state done and return at once.
     uint32_t host_rounds = 0, ahead = 8;
+    uint32_t front_next = front_applies() ? front_from : 0, front_wait = 16;
     while (!host.done) {
+      if (front_next && live_built && host.round >= front_next) {
+        // one more full round, from known colours, then frontier rounds for
+        // as long as they are cheap; where they were not, full rounds follow
+        hipLaunchKernelGGL(k_front_save, dim3(gn), dim3(kBlock), 0, s, ctx, front_ctx().prev);
+        if (int r = round_live()) return r;
+        if (host.done) break;
+        bool again = false, ran = false;
+        if (int r = front_rounds(&again, &ran)) return r;
+        if (again && !host.done) {
+          // stable by the frontier's account: a full round has the last word
+          if (int r = round_live()) return r;
+          front_next = 0;
+        } else {
+          front_next = host.round + front_wait;
+          if (!ran) front_wait = std::min<uint32_t>(2 * front_wait, 1u << 16);
+        }
+        continue;
+      }
       if (host_rounds < host_rounds_first) {
         if (int r = round_live()) return r;
         ++host_rounds;
@@ -1567,7 +1717,7 @@ struct Session {
   }
 
   // A graph that one workgroup's LDS holds goes through wl_small.h whole: the
-  // general path takes 0.6 ms or more for any graph, this one 0.05 ms for
+  // general path takes 0.6 ms or more for any graph, this one 0.07 ms for
   // 1500 nodes and 12,000 entries.  The bounds are the LDS (nodes) and where
   // one compute unit's loads of the columns cost as much as the general
   // path's launches (entries).  WL_SMALL=0, the tuning variables of the
@@ -1577,7 +1727,8 @@ struct Session {
     if (L.n > kSmallNodes || L.nnz > kSmallEntries || (diag && g_stats_flags)) return false;
     static const char* const names[] = {"WL_VALIDATE",    "WL_PB",          "WL_DEGREE_ROUND",
                                         "WL_HOST_ROUNDS", "WL_ASYNC_PASSES", "WL_GRAPH",
-                                        "WL_NT_STREAM",   "WL_SORT_FIX",     "WL_CHAIN_SPINS"};
+                                        "WL_NT_STREAM",   "WL_SORT_FIX",     "WL_CHAIN_SPINS",
+                                        "WL_FRONT"};
     for (const char* v : names)
       if (getenv(v)) return false;
     return env_int("WL_SMALL", 0, 1, 1) != 0;
@@ -1644,6 +1795,11 @@ int open_session(Session& S, const wl_csr* g, uint32_t* colors, void* ws,
   S.sym_flag = (g->flags & WL_CSR_SYMMETRIC) != 0;
   S.deg_mode = env_int("WL_DEGREE_ROUND", 0, 1, 1) != 0;
   S.use_graph = env_int("WL_GRAPH", 0, 1, 0) != 0;
+  {
+    // the tuning of the device-driven full rounds keeps them the rounds that run
+    const bool tuned = getenv("WL_HOST_ROUNDS") || getenv("WL_ASYNC_PASSES") || S.use_graph;
+    S.front_from = (uint32_t)env_int("WL_FRONT", 0, 1 << 30, tuned ? 0 : (int)kFrontFrom);
+  }
   if (wants_pb(g) && S.pb_mode != 0) {
     S.P = make_pb_layout(g->n, g->nnz);
     // pass 1 reads the column indices 16 bytes at a time
@@ -1898,14 +2054,7 @@ int wl_refine_round(const wl_csr* g, const uint32_t* color_in, uint32_t k_in,
   if (S.host.err & 4u) return fail(WL_EINVAL, "a colour is >= k_in");
   if (color_out != color_in)
     HIP_TRY(hipMemcpyAsync(color_out, color_in, 4 * g->n, hipMemcpyDeviceToDevice, S.s));
-  hipLaunchKernelGGL(k_count_colors, dim3(grid_for(k_in + 1)), dim3(kBlock), 0, S.s,
-                     S.ctx, k_in);
-  hipLaunchKernelGGL(k_hist_colors, dim3(gn), dim3(kBlock), 0, S.s, S.ctx);
-  // the class starts by the device-wide scan over the k_in sizes (st->k)
-  S.xscan(nullptr, &S.ctx.st->k, S.ctx.ids, nullptr, nullptr, nullptr, scan_blocks(k_in));
-  hipLaunchKernelGGL(k_starts_colors, dim3(grid_for(k_in + 1ull, kBlock, 4096)), dim3(kBlock), 0,
-                     S.s, S.ctx, k_in);
-  hipLaunchKernelGGL(k_place_colors, dim3(gn), dim3(kBlock), 0, S.s, S.ctx);
+  S.group_by_color(k_in);
   HIP_LAUNCH_CHECK();
   if (int r = S.stats_begin()) return r;
   if (int r = S.build_schedule()) return r;

@@ -47,17 +47,23 @@ struct SmallArgs {
   uint32_t max_rounds;
 };
 
-template <bool LCOL>
-struct SmallState {
-  uint64_t x[kSmallNodes];
-  unsigned long long key[kSmallNodes];
-  uint32_t cnt[kSmallNodes + 4];
-  uint16_t node[kSmallNodes];
-  uint16_t seg[kSmallNodes];
-  uint16_t slen[kSmallNodes + 4];
-  uint8_t used[kSmallNodes];
-  uint8_t head[kSmallNodes];
+// What the sort of up to N positions works on.
+template <uint32_t N>
+struct SortLds {
+  static constexpr uint32_t kPer = N / kSmallThreads;  // positions per thread
+  unsigned long long key[N];
+  uint32_t cnt[N + 4];
+  uint16_t node[N];
+  uint16_t seg[N];
+  uint16_t slen[N + 4];
+  uint8_t used[N];
   uint32_t sh[kSmallThreads / kWave];
+};
+
+template <bool LCOL>
+struct SmallState : SortLds<kSmallNodes> {
+  uint64_t x[kSmallNodes];
+  uint8_t head[kSmallNodes];
   uint32_t nmid, nlong, bad;
   // row starts and columns of a graph that fits (16 bits each), else the row
   // starts only
@@ -71,19 +77,20 @@ constexpr uint32_t kSmallPer = kSmallNodes / kSmallThreads;
 
 // cnt[0, n) -> its exclusive scan, cnt[n] = the total, which is returned.
 // Contains __syncthreads(), the last of them after the last write.
-template <bool LCOL>
-__device__ __forceinline__ uint32_t small_scan(SmallState<LCOL>& L, uint32_t n) {
-  const uint32_t i0 = kSmallPer * threadIdx.x;
-  uint32_t v[kSmallPer], s = 0;
+template <uint32_t N>
+__device__ __forceinline__ uint32_t small_scan(SortLds<N>& L, uint32_t n) {
+  constexpr uint32_t kPer = SortLds<N>::kPer;
+  const uint32_t i0 = kPer * threadIdx.x;
+  uint32_t v[kPer], s = 0;
 #pragma unroll
-  for (uint32_t u = 0; u < kSmallPer; ++u) {
+  for (uint32_t u = 0; u < kPer; ++u) {
     v[u] = i0 + u < n ? L.cnt[i0 + u] : 0u;
     s += v[u];
   }
   uint32_t tot;
   uint32_t run = pb_block_scan<kSmallThreads>(s, L.sh, &tot);
 #pragma unroll
-  for (uint32_t u = 0; u < kSmallPer; ++u)
+  for (uint32_t u = 0; u < kPer; ++u)
     if (i0 + u < n) {
       L.cnt[i0 + u] = run;
       run += v[u];
@@ -95,12 +102,13 @@ __device__ __forceinline__ uint32_t small_scan(SmallState<LCOL>& L, uint32_t n) 
 
 // Sorts the keys inside every segment (see the head of the file); on return
 // every segment holds one key.
-template <bool LCOL>
-__device__ __forceinline__ void small_sort(SmallState<LCOL>& L, uint32_t n) {
+template <uint32_t N>
+__device__ __forceinline__ void small_sort(SortLds<N>& L, uint32_t n) {
+  constexpr uint32_t kPer = SortLds<N>::kPer;
   while (true) {
     bool any = false;
 #pragma unroll
-    for (uint32_t u = 0; u < kSmallPer; ++u) {
+    for (uint32_t u = 0; u < kPer; ++u) {
       const uint32_t p = threadIdx.x + u * kSmallThreads;
       if (p >= n) break;
       L.cnt[p] = 0;
@@ -111,12 +119,12 @@ __device__ __forceinline__ void small_sort(SmallState<LCOL>& L, uint32_t n) {
       }
     }
     if (!__syncthreads_or(any)) return;
-    unsigned long long k[kSmallPer];
-    uint32_t nd[kSmallPer], slot[kSmallPer], at[kSmallPer], aux[kSmallPer];
-    uint8_t how[kSmallPer] = {};  // 0 stays, 1 ranked, 2 counted
+    unsigned long long k[kPer];
+    uint32_t nd[kPer], slot[kPer], at[kPer], aux[kPer];
+    uint8_t how[kPer] = {};  // 0 stays, 1 ranked, 2 counted
     bool counted = false;
 #pragma unroll
-    for (uint32_t u = 0; u < kSmallPer; ++u) {
+    for (uint32_t u = 0; u < kPer; ++u) {
       const uint32_t p = threadIdx.x + u * kSmallThreads;
       if (p >= n) break;
       const uint32_t s = L.seg[p], us = L.used[s];
@@ -153,7 +161,7 @@ __device__ __forceinline__ void small_sort(SmallState<LCOL>& L, uint32_t n) {
     // gives every counter's first position
     if (__syncthreads_or(counted)) small_scan(L, n);
 #pragma unroll
-    for (uint32_t u = 0; u < kSmallPer; ++u) {
+    for (uint32_t u = 0; u < kPer; ++u) {
       if (how[u] == 0) continue;
       uint32_t s = slot[u];
       uint32_t len = aux[u], bits = 0;

@@ -177,12 +177,6 @@ __device__ __forceinline__ K group_bitonic(K key, uint32_t lane) {
   return key;
 }
 
-// Lane of the r-th set bit of m (r from 0; 64 when there are fewer).
-__device__ __forceinline__ int nth_bit(unsigned long long m, int r) {
-  for (; r > 0 && m; --r) m &= m - 1;
-  return m ? __builtin_ctzll(m) : kWave;
-}
-
 constexpr uint32_t kVLane = 8;    // rows sorted by one lane in registers
 constexpr uint32_t kVGroup = 16;  // ... by 16 lanes; longer ones (<= 64) by the wave
 

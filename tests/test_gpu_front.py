@@ -1,0 +1,149 @@
+"""Frontier rounds (symmetric graphs of short rows): the oracle's colours,
+colour count and rounds bit for bit, entered after every early round
+(WL_FRONT), on graphs whose rounds mark few members of a class (one wave),
+many (a workgroup), all of them, and more than a workgroup takes (the round
+goes back to a full one), under a round cap, with labels and weights, with
+rows of every length that qualifies, in F_p and in Z/2^64."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2607_02603_amd as wl
+from paper_2607_02603_amd import inputs
+from weight_seeds import G, M, unmix
+
+pytestmark = pytest.mark.gpu
+
+
+def _csr(n, u, v):
+    return inputs.csr_from_edges(n, np.asarray(u), np.asarray(v))
+
+
+def _check(g, wt=None, init=None, seed=0, rp64=False, ring=False, max_rounds=0):
+    ref, kr, rr, _, st = oracle.stable_coloring(g.row_ptr, g.col, wt, init, seed, max_rounds,
+                                                q=64 if ring else 0)
+    rp = np.asarray(g.row_ptr, np.uint64)
+    dg = wl.Graph.from_numpy(g.n, rp if rp64 else rp.astype(np.uint32), g.col, wt,
+                             device="cuda", symmetric=True)
+    it = None if init is None else torch.from_numpy(
+        np.asarray(init, np.uint32).view(np.int32)).cuda()
+    print(f"n={g.n} nnz={g.nnz} colours={kr} rounds={rr}", flush=True)
+    with wl.precision(wl.WL_PRECISION_RING64 if ring else wl.WL_PRECISION_FP):
+        c, k, r = wl.wl_stable_coloring(dg, it, seed, max_rounds, allow_max_rounds=True)
+    assert (k, r) == (kr, rr)
+    assert np.array_equal(c.cpu().numpy().view(np.uint32), ref)
+
+
+def _tree(n, seed, window):
+    rng = np.random.default_rng(seed)
+    i = np.arange(1, n)
+    return _csr(n, i, i - 1 - (rng.random(n - 1) * np.minimum(i, window)).astype(np.int64))
+
+
+def _spider(legs, length):
+    """'legs' equal paths from one centre through a binary tree (short rows)."""
+    u, v = [], []
+    ids = list(range(legs))
+    nxt = legs
+    while len(ids) > 1:
+        new = []
+        for a in range(0, len(ids), 2):
+            for x in ids[a:a + 2]:
+                u.append(x)
+                v.append(nxt)
+            new.append(nxt)
+            nxt += 1
+        ids = new
+    base = nxt
+    for t in range(length):
+        for x in range(legs):
+            u.append(x if t == 0 else base + (t - 1) * legs + x)
+            v.append(base + t * legs + x)
+    return _csr(base + legs * length, u, v)
+
+
+GRAPHS = {
+    "grid": lambda: inputs.grid_graph(70, 90),
+    "grid_thin": lambda: inputs.grid_graph(2, 4000),
+    "path": lambda: inputs.grid_graph(1, 5001),
+    "tree": lambda: _tree(6000, 1, 3),
+    "tree_bushy": lambda: _tree(9000, 2, 40),
+    "spider": lambda: _spider(128, 70),
+    "er": lambda: inputs.er_graph(6000, 9000, seed=4),
+}
+
+
+@pytest.mark.parametrize("name", sorted(GRAPHS))
+@pytest.mark.parametrize("front", [0, 1, 2, 5])
+def test_entered_after_every_early_round(monkeypatch, name, front):
+    monkeypatch.setenv("WL_FRONT", str(front))
+    _check(GRAPHS[name](), seed=front, rp64=front == 2)
+
+
+@pytest.mark.parametrize("name", ["grid", "tree", "spider"])
+def test_default_entry_weights_labels_ring(name):
+    g = GRAPHS[name]()
+    _check(g, seed=1)
+    _check(g, seed=1, ring=True)
+    _check(g, init=(np.arange(g.n) % 997 == 0), seed=2)
+    # symmetric weights, zeros among them: a value of the unordered pair
+    u = np.repeat(np.arange(g.n), np.diff(np.asarray(g.row_ptr, np.int64)))
+    lo, hi = np.minimum(u, g.col), np.maximum(u, g.col)
+    wt = ((lo * 7 + hi * 7) % 5 % 3).astype(np.uint32)
+    _check(g, wt, seed=3)
+    _check(g, wt, seed=3, ring=True)  # weighted: full rounds in Z/2^64
+
+
+@pytest.mark.parametrize("cap", [3, 4, 9, 17, 34])
+def test_round_cap(monkeypatch, cap):
+    monkeypatch.setenv("WL_FRONT", "2")
+    _check(inputs.grid_graph(70, 90), seed=1, max_rounds=cap)
+
+
+@pytest.mark.parametrize("legs,length", [(63, 100), (64, 100), (65, 100), (2000, 12), (8192, 6),
+                                         (8300, 6)])
+def test_marked_members_of_one_class(monkeypatch, legs, length):
+    # every round marks all members of classes of 'legs' nodes: one wave up
+    # to 64, a workgroup up to 8192, and beyond that the full rounds
+    monkeypatch.setenv("WL_FRONT", "1")
+    _check(_spider(legs, length), seed=legs)
+
+
+@pytest.mark.parametrize("deg", [4, 5, 8, 9, 16, 63, 64, 65])
+def test_row_lengths(monkeypatch, deg):
+    # a path whose every 50th node carries pendant nodes up to degree 'deg'
+    monkeypatch.setenv("WL_FRONT", "1")
+    n0 = 3000
+    hubs = np.arange(0, n0, 50)
+    pend = deg - 2
+    u = np.concatenate([np.arange(n0 - 1), np.repeat(hubs, pend)])
+    v = np.concatenate([np.arange(1, n0), n0 + np.arange(hubs.size * pend)])
+    g = _csr(n0 + hubs.size * pend + 2000, u, v)  # and isolated nodes
+    _check(g, seed=deg)
+    _check(g, seed=deg, ring=True)
+
+
+def test_wide_grid_goes_back_to_full_rounds(monkeypatch):
+    # 2 x (300 + 9000) outline: more than 8192 members are marked at once
+    monkeypatch.setenv("WL_FRONT", "2")
+    _check(inputs.grid_graph(12, 9000), seed=5)
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("rnd", [2, 3, 4, 11, 20])
+def test_degenerate_value_in_a_round(monkeypatch, rnd, ring):
+    # a seed that makes one colour's value 0 (in Z/2^64: 2^60 or 0) in a round
+    # before, at and after the change to frontier rounds: the round is left to
+    # the full rounds
+    monkeypatch.setenv("WL_FRONT", "2")
+    g = inputs.grid_graph(70, 90)
+    for b in (0, 1, 5):
+        for w in (0, 1 << 60) if ring else (0,):
+            _check(g, seed=_seed_for_weight(w, rnd, b), ring=ring)
+
+
+def _seed_for_weight(w, rnd, b):
+    key = (unmix(w) - (b + 1) * G) & M
+    s1 = (unmix(key) - (rnd + 1) * G) & M
+    return (unmix(s1) - G) & M
