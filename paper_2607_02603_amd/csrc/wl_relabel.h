@@ -438,7 +438,7 @@ struct SmallLds {
 
 // One workgroup per small segment, keys in LDS: a counting sort by the ten
 // bits at and below the highest bit in which the keys differ, whose mixed
-// buckets of at most ctx.cs_fix (default kCsFix) keys are sorted by insertion;
+// buckets of at most ctx.cs_fix (default kCsFix) keys are ranked by pairs;
 // a larger mixed bucket (rare for hashed images) falls back to a bitonic sort
 // of (z, node).
 // Then flags where z changes.
@@ -518,9 +518,14 @@ __device__ __forceinline__ void small_sort_body(const Ctx& ctx, SmallLds& L, uin
     }
     // Counting sort by the kCsBits bits at and below the highest bit in which
     // the keys differ (above it they all agree), into inv (position ->
-    // element); then a bucket whose keys are not all equal is sorted by
-    // insertion when it holds at most ctx.cs_fix keys, and a larger one sends the
-    // segment to the sorting network below.
+    // element); then every member of a bucket whose keys are not all equal
+    // takes its rank among them when it holds at most ctx.cs_fix keys, and a
+    // larger one sends the segment to the sorting network below.  (Insertion
+    // by one thread per bucket was a serial chain of LDS accesses that the
+    // launch waited for: k_sorts 14 -> 10 us a round on a 20,000-node graph,
+    // 2.71 -> 2.31 ms a call on R-MAT 27.)  The inner loop stays rolled:
+    // unrolled inside the eight members it takes 163 registers, and the
+    // kernel a wave less per SIMD.
     const int top = 63 - __clzll((long long)xo);  // xo != 0: the keys differ
     const int sh = top >= (int)kCsBits - 1 ? top - ((int)kCsBits - 1) : 0;
     uint32_t rk[kSmallMax / kBlock];
@@ -561,23 +566,35 @@ __device__ __forceinline__ void small_sort_body(const Ctx& ctx, SmallLds& L, uin
       if (p > cnt[d] && k != skey[inv[p - 1]]) mixed[d] = 1;
     }
     __syncthreads();
-    for (uint32_t b = threadIdx.x; b < kCsBuckets; b += kBlock) {
-      if (!mixed[b]) continue;
-      const uint32_t o = cnt[b], c = cnt[b + 1] - o;
+    uint32_t el[kSmallMax / kBlock], at[kSmallMax / kBlock];
+#pragma unroll
+    for (uint32_t j = 0; j < kSmallMax / kBlock; ++j) {
+      const uint32_t p = threadIdx.x + j * kBlock;
+      if (p >= len) break;
+      const uint32_t e = inv[p];
+      const unsigned long long k = skey[e];
+      const uint32_t d = (uint32_t)(k >> sh) & (kCsBuckets - 1);
+      el[j] = e;
+      at[j] = p;
+      if (!mixed[d]) continue;
+      const uint32_t o = cnt[d], c = cnt[d + 1] - o;
       if (c > ctx.cs_fix) {
         fallback = 1;
         continue;
       }
-      for (uint32_t i = o + 1; i < o + c; ++i) {
-        const uint16_t e = inv[i];
-        const unsigned long long k = skey[e];
-        uint32_t j = i;
-        while (j > o && skey[inv[j - 1]] > k) {
-          inv[j] = inv[j - 1];
-          --j;
-        }
-        inv[j] = e;
+      uint32_t r = o;
+#pragma unroll 1
+      for (uint32_t q = o; q < o + c; ++q) {
+        const unsigned long long kq = skey[inv[q]];
+        r += (kq < k || (kq == k && q < p)) ? 1u : 0u;
       }
+      at[j] = r;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < kSmallMax / kBlock; ++j) {
+      if (threadIdx.x + j * kBlock >= len) break;
+      inv[at[j]] = (uint16_t)el[j];
     }
     __syncthreads();
     if (!fallback) {
@@ -730,12 +747,12 @@ __device__ __forceinline__ void pico_sort_body(const Ctx& ctx, uint32_t bid, uin
 
 // Segments of kTinyMax + 1 .. kMidMax keys, one wave each (four per
 // workgroup, no workgroup barrier): a counting sort in LDS on the kMidBits
-// bits at and below the highest bit in which the keys differ, lane l owning
-// buckets kMidPer * l ..; a bucket whose keys differ is sorted by its lane by
-// insertion when it holds at most ctx.cs_fix keys (as in the small sort), and
-// a larger one sends the segment to a bitonic network in LDS.  A wave's LDS accesses are ordered by
-// the wave itself (the LDS executes a wave's instructions in order); the
-// fences only keep the compiler from moving them across a step.
+// bits at and below the highest bit in which the keys differ; the members of a
+// bucket whose keys differ take their ranks in it when it holds at most
+// ctx.cs_fix keys (as in the small sort), and a larger one sends the segment to
+// a bitonic network in LDS.  A wave's LDS accesses are ordered by the wave
+// itself (the LDS executes a wave's instructions in order); the fences only
+// keep the compiler from moving them across a step.
 constexpr uint32_t kMidBits = 9, kMidBuckets = 1u << kMidBits;
 constexpr uint32_t kMidWaves = 1024;  // fewer mid segments go to the workgroup sort
 constexpr uint32_t kMidPer = kMidMax / kWave;  // keys, and buckets, per lane
@@ -831,29 +848,49 @@ __device__ __forceinline__ void mid_sort_body(const Ctx& ctx, MidLds* lds, uint3
       if (t < len) L.inv[L.cnt[(kr[u] >> sh) & (kMidBuckets - 1)] + rk[u]] = (uint16_t)t;
     }
     wave_lds_step();
-    // each lane fixes its own buckets
-    bool too_big = false;
+    // buckets whose keys differ: the top bit of their count (every writer of a
+    // count stores the same value); then every member's rank in its bucket
+    constexpr uint32_t kMix = 0x80000000u;
 #pragma unroll
     for (uint32_t u = 0; u < kMidPer; ++u) {
-      const uint32_t b = lane * kMidPer + u;
-      const uint32_t o = L.cnt[b], c = L.cnt[b + 1] - o;
-      if (c < 2) continue;
+      const uint32_t p = lane + kWave * u;
+      if (p >= len) continue;
+      const unsigned long long k = L.skey[L.inv[p]];
+      const uint32_t b = (uint32_t)(k >> sh) & (kMidBuckets - 1);
+      const uint32_t o = L.cnt[b] & ~kMix;
+      if (p != o && k != L.skey[L.inv[o]]) L.cnt[b] = o | kMix;
+    }
+    wave_lds_step();
+    bool too_big = false;
+    uint32_t el[kMidPer], at[kMidPer];
+#pragma unroll
+    for (uint32_t u = 0; u < kMidPer; ++u) {
+      const uint32_t p = lane + kWave * u;
+      el[u] = at[u] = 0;
+      if (p >= len) continue;
+      const uint32_t e = L.inv[p];
+      const unsigned long long k = L.skey[e];
+      const uint32_t b = (uint32_t)(k >> sh) & (kMidBuckets - 1);
+      const uint32_t raw = L.cnt[b], o = raw & ~kMix, c = (L.cnt[b + 1] & ~kMix) - o;
+      el[u] = e;
+      at[u] = p;
+      if (!(raw & kMix)) continue;
       if (c > ctx.cs_fix) {
-        for (uint32_t i = o + 1; i < o + c; ++i)
-          if (L.skey[L.inv[i]] != L.skey[L.inv[o]]) too_big = true;
+        too_big = true;
         continue;
       }
-      for (uint32_t i = o + 1; i < o + c; ++i) {
-        const uint16_t e = L.inv[i];
-        const unsigned long long k = L.skey[e];
-        uint32_t j = i;
-        while (j > o && L.skey[L.inv[j - 1]] > k) {
-          L.inv[j] = L.inv[j - 1];
-          --j;
-        }
-        L.inv[j] = e;
+      uint32_t r = o;
+#pragma unroll 1
+      for (uint32_t q = o; q < o + c; ++q) {
+        const unsigned long long kq = L.skey[L.inv[q]];
+        r += (kq < k || (kq == k && q < p)) ? 1u : 0u;
       }
+      at[u] = r;
     }
+    wave_lds_step();
+#pragma unroll
+    for (uint32_t u = 0; u < kMidPer; ++u)
+      if (lane + kWave * u < len) L.inv[at[u]] = (uint16_t)el[u];
     wave_lds_step();
     if (__ballot(too_big) == 0) {
 #pragma unroll
