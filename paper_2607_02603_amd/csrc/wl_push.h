@@ -451,7 +451,7 @@ __global__ void __launch_bounds__(kBlock) k_pb_cursors(Ctx ctx, PbCtx pb) {
   }
 }
 
-__global__ void __launch_bounds__(kPbThreads) k_pb_scatter2(Ctx ctx, PbCtx pb) {
+__global__ void __launch_bounds__(kPbThreads) k_pb_scatter2(Ctx ctx, PbCtx pb, int by_bin) {
   if (ctx.st->done || (ctx.st->err & kErrNotSymmetric)) return;
   __shared__ __align__(16) uint32_t buf[kPbTile2];
   __shared__ uint32_t hist[kPbMaxFine];
@@ -460,10 +460,24 @@ __global__ void __launch_bounds__(kPbThreads) k_pb_scatter2(Ctx ctx, PbCtx pb) {
   const uint32_t nf = 1u << pb.fbits;
   const uint32_t cmask = (1u << pb.cbits) - 1;
   constexpr uint32_t kPer = kPbTile2 / kPbThreads;
-  // block v: tile v / nb1 of coarse bin v % nb1 (neighbouring blocks work on
-  // different coarse bins, so their cursor reservations do not collide)
-  const uint32_t cb = blockIdx.x % pb.nb1, r = blockIdx.x / pb.nb1;
-  if (pb.tile2_off[cb] + r >= pb.tile2_off[cb + 1]) return;
+  uint32_t cb, r;  // the block's tile is the r-th of coarse bin cb
+  if (by_bin) {
+    // block v: tile v / nb1 of coarse bin v % nb1 (neighbouring blocks work on
+    // different coarse bins, so their cursor reservations do not collide)
+    cb = blockIdx.x % pb.nb1;
+    r = blockIdx.x / pb.nb1;
+    if (pb.tile2_off[cb] + r >= pb.tile2_off[cb + 1]) return;
+  } else {
+    // a block per tile, in a permuted order (tile_order): blocks that run at
+    // one time then work on the bins in proportion to their tiles
+    const uint32_t nt = pb.tile2_off[pb.nb1];
+    if (blockIdx.x >= nt) return;
+    const uint32_t tile = tile_order(blockIdx.x, nt);
+    static_assert(kPbMaxBins <= kPbThreads, "one thread per coarse bin");
+    // its bin: the last one whose first tile is not beyond it
+    cb = __syncthreads_count(threadIdx.x < pb.nb1 && pb.tile2_off[threadIdx.x] <= tile) - 1;
+    r = tile - pb.tile2_off[cb];
+  }
   const uint64_t a0 = pb.bstart1[cb] + (uint64_t)r * kPbTile2;
   const uint32_t cnt = (uint32_t)(min(pb.bstart1[cb + 1], a0 + kPbTile2) - a0);
   uint32_t rec[kPer];

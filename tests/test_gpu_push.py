@@ -118,6 +118,19 @@ def test_two_scatter_passes(force_pb):
     _exact(g.row_ptr, g.col, seed=2)
 
 
+@pytest.mark.parametrize("hubs", [9000, 40000])
+def test_two_scatter_passes_with_one_large_bin(force_pb, hubs):
+    # node ids in degree order: nearly all entries in the first coarse bin, so
+    # that pass 2 takes its tiles in permuted order; the last bin is cut short
+    rng = np.random.default_rng(hubs)
+    n = 256 * 8192 + 12345
+    u = np.concatenate([rng.integers(0, hubs, 60000), rng.integers(0, n, 4000)])
+    v = np.concatenate([rng.integers(0, hubs, 60000), rng.integers(0, n, 4000)])
+    g = inputs.csr_from_edges(n, u, v)
+    _say(f"skewed n={n} nnz={g.nnz}")
+    _exact(g.row_ptr, g.col, seed=4)
+
+
 def test_refine_round_each_round(force_pb):
     g = inputs.rmat(13, 8, seed=1)
     dg = _sym_graph(g.row_ptr, g.col)
