@@ -180,7 +180,9 @@ int wl_stable_coloring_noalloc(const wl_csr *g, const uint32_t *init_color,
  * page-locked staging buffers and copied to the device in chunks of at most
  * 64M entries, on a copy stream of the library's own, while the device
  * computes the images of the previous chunk; the colours, images and the
- * relabel stay in the workspace.  The rounds, seeds and colour ids are those
+ * relabel stay in the workspace.  When the entry arrays are page-locked, a
+ * round that needs at least 3/4 of the entries copies them all from there,
+ * unpacked, and chunks have at most 16M entries.  The rounds, seeds and colour ids are those
  * of wl_stable_coloring: for the same graph, labels and seed both return
  * the same colours, colour count and round count.
  *   g_host      host CSR (pageable or page-locked), n < 2^31.
@@ -190,8 +192,9 @@ int wl_stable_coloring_noalloc(const wl_csr *g, const uint32_t *init_color,
  *               gives the size with full chunks (about 69 bytes per node
  *               plus two chunks); a smaller one, down to chunks of 4096
  *               entries, is accepted.  Room beyond that size is used too:
- *               once all chunks of a round fit there, they are kept and the
- *               later rounds need no transfers.  Its contents are scratch.
+ *               once all chunks of a round fit behind the node state, they are
+ *               kept and the later rounds need no transfers.  Its contents
+ *               are scratch.
  * The call also allocates about 2 x 13 bytes (17 weighted) per chunk entry
  * of page-locked host memory, and up to about 25 bytes per node of pageable
  * host memory (the rows a round needs and their segment offsets), freed on

@@ -402,6 +402,21 @@ struct StreamPlan {
   RawBuf<uint64_t> seg0, ent0;
   uint64_t nr = 0, ns = 0, ne = 0;
 
+  // entries of the rows with act set
+  static uint64_t active_entries(HostPool& pool, const HostGraph& G, const uint8_t* act) {
+    const unsigned T = pool.size();
+    std::vector<uint64_t> te(T, 0);
+    pool.run([&](unsigned t) {
+      uint64_t en = 0;
+      for_active(act, G.n * t / T, G.n * (t + 1) / T,
+                 [&](uint64_t i) { en += G.rp(i + 1) - G.rp(i); });
+      te[t] = en;
+    });
+    uint64_t e = 0;
+    for (uint64_t x : te) e += x;
+    return e;
+  }
+
   // false when the host arrays cannot be allocated
   bool build(HostPool& pool, const HostGraph& G, const uint8_t* act) {
     const unsigned T = pool.size();
@@ -476,7 +491,8 @@ struct StreamPlan {
   // Packs segments [a, b) into the staging arrays: node (b - a), off
   // (b - a + 1, chunk-relative), col / wt (the chunk's entries; wt only for
   // a weighted G) and fold.  Returns the number of folds, or -1 if more
-  // than fold_cap were needed.
+  // than fold_cap were needed.  col NULL: the entries are not packed (a plan
+  // of all rows, whose packed entries are G's own in order).
   int64_t pack(HostPool& pool, const HostGraph& G, uint64_t a, uint64_t b, uint32_t* node,
                uint64_t* off, uint32_t* col, uint32_t* wt, StreamFold* fold,
                uint64_t fold_cap) const {
@@ -502,7 +518,7 @@ struct StreamPlan {
       uint64_t r = row_of(ga);
       uint64_t run_src = 0, run_dst = 0, run_len = 0;
       auto flush = [&] {
-        if (!run_len) return;
+        if (!run_len || !col) return;
         memcpy(col + run_dst, G.col + run_src, 4 * run_len);
         if (weighted) memcpy(wt + run_dst, G.wt + run_src, 4 * run_len);
         run_len = 0;

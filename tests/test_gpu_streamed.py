@@ -106,6 +106,30 @@ def test_kept_chunks_with_cut_rows(extra):
         assert np.array_equal(c.numpy().view(np.uint32), co)
 
 
+@pytest.mark.parametrize("pinned", [True, False])
+@pytest.mark.parametrize("chunk,extra", [(4096, 0), (7001, 0), (7001, 1 << 16), (10**6, 0)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_entries_packed_or_copied_in_place(pinned, chunk, extra, weighted):
+    # page-locked entry arrays: a round that needs most entries copies them
+    # from there (rows cut at chunk ends, empty rows between), the later ones
+    # pack; pageable arrays are packed in every round; the chunks of a round
+    # are kept where the workspace behind the node state holds them
+    rng = random.Random(chunk)
+    n = 5001
+    edges = [(7, 8 + rng.randrange(n - 8)) for _ in range(9000)]
+    edges += [(rng.randrange(n // 2), rng.randrange(n)) for _ in range(30001)]
+    rp, col = bf.to_csr(n, edges, directed=True)
+    wt = np.array([rng.randint(1, 5) for _ in range(col.size)], np.uint32) if weighted else None
+    init = np.array([rng.choice([0, 3]) for _ in range(n)], np.uint32)
+    for lab in (None, init):
+        g = _host_graph(rp, col, wt, pinned)
+        c, k, r = wl.wl_stable_coloring_streamed(
+            g, _init_t(lab), 6, ws_bytes=_ws_for_chunk(n, chunk, weighted) + extra)
+        co, ko, ro, _, st = oracle.stable_coloring(rp, col, wt, lab, 6)
+        assert st == 0 and (k, r) == (ko, ro)
+        assert np.array_equal(c.numpy().view(np.uint32), co)
+
+
 def test_rmat_many_chunks_pageable():
     g = inputs.rmat(14, 16, seed=9)
     print(f"rmat14 nnz={g.nnz}", flush=True)
