@@ -301,6 +301,7 @@ __global__ void __launch_bounds__(kBlock) k_front_touch(Ctx ctx, FrontCtx F, uin
 constexpr uint32_t kFrontKeys = 256, kFrontSlots = 1024, kFrontProbes = 64;
 constexpr uint32_t kFrontBig = 16;       // workgroups for the big classes
 constexpr uint32_t kFrontBigList = kSmallThreads / kFrontBig;
+constexpr uint32_t kFrontPerBlock = 8;   // classes of a workgroup of the others (at most 16)
 
 struct FrontLds {
   unsigned long long key[kFrontMax];
@@ -316,33 +317,40 @@ struct FrontLds {
   uint32_t heads[kFrontMax / 32];  // all pairs: first places of the parts
   uint32_t hpre[kFrontMax / 32];   // ... parts before each word
   uint32_t big[kFrontBigList];
+  unsigned long long wx[kSmallThreads / kWave];
   uint32_t sh[kSmallThreads / kWave];
   uint32_t rep, lt, eq, best, rs, rlen, nh, nm, base, so, nkeys, many;
   unsigned long long z0;
 };
 static_assert(sizeof(FrontLds) <= 160 * 1024, "one workgroup's LDS");
 
-// What a split records: colour -> its parts, the class counts, and room in
-// the next S.  Returns (first new class index, first slot of the next S).
-__device__ __forceinline__ uint2 front_record(const FrontCtx& F, FrontRound* cur, uint32_t c,
-                                              uint32_t extra, uint32_t qn, uint32_t ret,
-                                              uint32_t size) {
-  const uint32_t b = F.color[c];
-  const unsigned long long o = atomicAdd(&cur->alloc, ((unsigned long long)extra << 32) | qn);
-  const uint32_t base = cur->k + (uint32_t)(o >> 32);
+// What a split records under its class's colour b: its parts (class indices
+// from 'base' on), and the class's new size.
+__device__ __forceinline__ void front_record(const FrontCtx& F, uint32_t c, uint32_t b,
+                                             uint32_t extra, uint32_t base, uint32_t ret,
+                                             uint32_t size) {
   F.ex[b] = extra;
   F.exbase[b] = base;
   F.exret[b] = ret;
   atomicAdd(&F.bsum[b / kFrontChunk], extra);
-  F.size[c] = size - qn;
-  return make_uint2(base, (uint32_t)o);
+  F.size[c] = size;
 }
 
-// A class with at most kFrontWave marked members, by one wave.
+// A class with at most kFrontWave marked members, by one wave, in two steps:
+// the parts, then (with class indices and room in the next S taken for all
+// waves of the workgroup at once) what follows from them.
+struct FrontWave {
+  uint32_t c, b, t, s, m;      // class, colour, marked members, first member, size
+  uint32_t v, pos, at_end;     // the lane's marked member, its place; a member at the end
+  uint32_t gi, glen;           // its part in order; at a part's first lane, its length
+  uint32_t ret, rs, rlen;      // the part that stays, its marked members
+  uint32_t extra, qn;          // parts added, members split off
+  bool head, eq;
+};
+
 template <bool RP64, bool W>
-__device__ __forceinline__ void front_split_wave(const Ctx& ctx, const FrontCtx& F,
-                                                 FrontRound* cur, uint32_t i, uint32_t c,
-                                                 uint64_t rkey) {
+__device__ __forceinline__ void front_wave_parts(const Ctx& ctx, const FrontCtx& F, uint32_t i,
+                                                 uint32_t c, uint64_t rkey, FrontWave& X) {
   const uint32_t lane = lane_id(), tag = i + 1;
   const uint32_t t = F.tc[c], s = F.start[c], m = F.size[c];
   if (m < 2) return;
@@ -384,7 +392,7 @@ __device__ __forceinline__ void front_split_wave(const Ctx& ctx, const FrontCtx&
     }
   }
   const unsigned long long prev = __shfl_up(key, 1, kWave);
-  const unsigned long long below = (1ull << lane) - 1, upto = (2ull << lane) - 1;
+  const unsigned long long upto = (2ull << lane) - 1;
   const bool in = lane < t;
   const bool head = in && (lane == 0 || key != prev);
   const unsigned long long hb = __ballot(head);
@@ -414,23 +422,43 @@ __device__ __forceinline__ void front_split_wave(const Ctx& ctx, const FrontCtx&
     rs = (uint32_t)nth_bit(hb, (int)ret);
   }
   if (G == 1) return;
-  const uint32_t qn = t - rlen, cut = s + m - qn;
+  X.c = c;
+  X.b = F.color[c];
+  X.t = t;
+  X.s = s;
+  X.m = m;
+  X.v = v;
+  X.gi = gi;
+  X.glen = glen;
+  X.ret = ret;
+  X.rs = rs;
+  X.rlen = rlen;
+  X.extra = G - 1;
+  X.qn = t - rlen;
+  X.head = head;
+  X.eq = eq;
+  // loaded before the workgroup's atomic is waited for: where the members
+  // are, and who is at the end of the class
+  X.pos = in && !(lane >= rs && lane < rs + rlen) ? F.posn[v] : 0u;
+  X.at_end = t < m && lane < X.qn ? F.mem[s + m - X.qn + lane] : 0u;
+}
+
+__device__ __forceinline__ void front_wave_emit(const FrontCtx& F, uint32_t i, const FrontWave& X,
+                                                uint32_t base, uint32_t so) {
+  const uint32_t lane = lane_id();
+  const unsigned long long below = (1ull << lane) - 1;
+  const uint32_t t = X.t, s = X.s, m = X.m, v = X.v, rs = X.rs, rlen = X.rlen, qn = X.qn;
+  const uint32_t cut = s + m - qn, pos = X.pos;
+  if (lane == 0) front_record(F, X.c, X.b, X.extra, base, X.ret, m - qn);
+  const bool in = lane < t;
   const bool off_part = in && !(lane >= rs && lane < rs + rlen);
-  // loaded before the record's atomic is waited for: where the members are,
-  // and who is at the end of the class
-  const uint32_t pos = off_part ? F.posn[v] : 0u;
-  const uint32_t at_end = t < m && lane < qn ? F.mem[cut + lane] : 0u;
-  uint2 rec = make_uint2(0, 0);
-  if (lane == 0) rec = front_record(F, cur, c, G - 1, qn, ret, m);
-  const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)rec.x, 0);
-  const uint32_t so = (uint32_t)__builtin_amdgcn_readlane((int)rec.y, 0);
   const uint32_t off = lane < rs ? lane : lane - rlen;  // rank among the split-off members
-  const uint32_t q = gi + ((t < m && !eq && gi >= ret) ? 1u : 0u);
-  const uint32_t id = base + (q < ret ? q : q - 1);
+  const uint32_t q = X.gi + ((t < m && !X.eq && X.gi >= X.ret) ? 1u : 0u);
+  const uint32_t id = base + (q < X.ret ? q : q - 1);
   if (off_part) {
-    if (head) {
+    if (X.head) {
       F.start[id] = cut + off;
-      F.size[id] = glen;
+      F.size[id] = X.glen;
     }
     F.S[(i + 1) & 1][so + off] = v;
     F.scls[so + off] = id;
@@ -441,7 +469,7 @@ __device__ __forceinline__ void front_split_wave(const Ctx& ctx, const FrontCtx&
     unsigned long long occ = (off_part && pos >= cut) ? 1ull << (pos - cut) : 0ull;
     for (int o = kWave / 2; o > 0; o >>= 1) occ |= __shfl_xor(occ, o, kWave);
     const bool mv = lane < qn && !((occ >> lane) & 1);
-    const uint32_t w = at_end;
+    const uint32_t w = X.at_end;
     const unsigned long long holes = __ballot(off_part && pos < cut);
     const uint32_t j = (uint32_t)__popcll(__ballot(mv) & below);
     const uint32_t hp = (uint32_t)__shfl((int)pos, nth_bit(holes, (int)j) & (kWave - 1), kWave);
@@ -514,12 +542,19 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
   // an unmarked member is among the first t + 1; the last wave takes its
   // image while the others go on
   if (t < m) {
-    for (uint32_t p0 = 0; p0 <= t; p0 += kSmallThreads) {
+    // (a long class is sampled first: its first members may all be marked)
+    const uint32_t spread = m / kSmallThreads;
+    if (spread >= 4) {
+      const uint32_t p = threadIdx.x * spread;
+      const unsigned long long un = __ballot(F.stamp[F.mem[s + p]] != tag);
+      if (un && (int)lane == __builtin_ctzll(un)) atomicMin(&L.rep, p);
+      __syncthreads();
+    }
+    for (uint32_t p0 = 0; L.rep == 0xFFFFFFFFu && p0 <= t; p0 += kSmallThreads) {
+      __syncthreads();  // the loop's condition is read by all before it changes
       const uint32_t p = p0 + threadIdx.x;
       const unsigned long long un = __ballot(p <= t && F.stamp[F.mem[s + min(p, t)]] != tag);
       if (un && (int)lane == __builtin_ctzll(un)) atomicMin(&L.rep, p);
-      __syncthreads();
-      if (L.rep != 0xFFFFFFFFu) break;  // uniform: read between two barriers
       __syncthreads();
     }
     if (wid == kHashWaves) {
@@ -665,9 +700,12 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
   }
   const uint32_t qn = t - rlen, cut = s + m - qn;
   if (threadIdx.x == 0) {
-    const uint2 rec = front_record(F, cur, c, G - 1, qn, ret, m);
-    L.base = rec.x;
-    L.so = rec.y;
+    const uint32_t b = F.color[c];
+    const unsigned long long o =
+        atomicAdd(&cur->alloc, ((unsigned long long)(G - 1) << 32) | qn);
+    L.base = cur->k + (uint32_t)(o >> 32);
+    L.so = (uint32_t)o;
+    front_record(F, c, b, G - 1, L.base, ret, m - qn);
   }
   __syncthreads();
   const uint32_t base = L.base, so = L.so;
@@ -759,13 +797,43 @@ __global__ void __launch_bounds__(kSmallThreads) k_front_split(Ctx ctx, FrontCtx
   if (cur->done || cur->overflow) return;
   const uint32_t nd = cur->nd;
   const uint64_t rkey = round_key(ctx.st->seed, cur->round);
+  const uint32_t lane = lane_id(), w = threadIdx.x / kWave;
+  constexpr uint32_t kWaves = kSmallThreads / kWave;
   if (blockIdx.x >= kFrontBig) {
-    // neighbours in the list go to different workgroups: a few hundred classes
-    // then take a compute unit each
-    const uint32_t nb = gridDim.x - kFrontBig, nw = nb * (kSmallThreads / kWave);
-    for (uint32_t d = threadIdx.x / kWave * nb + blockIdx.x - kFrontBig; d < nd; d += nw) {
-      const uint32_t c = F.dirty[d];
-      if (F.tc[c] <= kFrontWave) front_split_wave<RP64, W>(ctx, F, cur, i, c, rkey);
+    // kFrontPerBlock classes to a workgroup, neighbours in the list in
+    // different ones.  One atomic per workgroup takes the class indices and the room in
+    // the next S: one per class, on the same address, was 8 of the 25 us
+    // of this launch for 789 classes.
+    const uint32_t nb = min(gridDim.x - kFrontBig, (nd + kFrontPerBlock - 1) / kFrontPerBlock);
+    const uint32_t blk = blockIdx.x - kFrontBig;
+    if (blk >= nb) return;
+    // 'd0' is the same for the whole workgroup
+    for (uint64_t d0 = 0; d0 < nd; d0 += (uint64_t)nb * kWaves) {
+      const uint64_t d = d0 + (uint64_t)w * nb + blk;
+      FrontWave X{};
+      if (d < nd) {
+        const uint32_t c = F.dirty[d];
+        if (F.tc[c] <= kFrontWave) front_wave_parts<RP64, W>(ctx, F, i, c, rkey, X);
+      }
+      if (lane == 0) L.wx[w] = ((unsigned long long)X.extra << 32) | X.qn;
+      __syncthreads();
+      if (w == 0) {
+        unsigned long long x = lane < kWaves ? L.wx[lane] : 0ull, inc = x;
+#pragma unroll
+        for (int o = 1; o < (int)kWaves; o <<= 1) {
+          const unsigned long long y = __shfl_up(inc, o, kWave);
+          if ((int)lane >= o) inc += y;
+        }
+        const unsigned long long tot = read_lane64(inc, (int)kWaves - 1);
+        unsigned long long o = 0;
+        if (lane == 0 && tot) o = atomicAdd(&cur->alloc, tot);
+        o = read_lane64(o, 0);
+        if (lane < kWaves) L.wx[lane] = o + inc - x;
+      }
+      __syncthreads();
+      const unsigned long long o = L.wx[w];
+      if (X.extra) front_wave_emit(F, i, X, cur->k + (uint32_t)(o >> 32), (uint32_t)o);
+      __syncthreads();  // wx is read before the next step's write
     }
     return;
   }
