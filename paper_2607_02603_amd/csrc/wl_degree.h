@@ -13,6 +13,7 @@
 // A graph with more distinct values than kDegRanks takes the general path.
 #pragma once
 #include "wl_live.h"
+#include "wl_small.h"
 
 namespace wl {
 
@@ -103,45 +104,30 @@ __global__ void __launch_bounds__(kDegThreads) k_deg_ranks(Ctx ctx, DegScratch d
   DevState* st = ctx.st;
   const uint32_t D = *d.nd;
   if (D > kDegRanks) return;  // the host takes the general path
-  __shared__ unsigned long long key[kDegRanks];
+  static_assert(kDegThreads == kSmallThreads, "small_sort");
+  __shared__ SortLds<kDegRanks> L;
+  unsigned long long* const key = L.key;
   __shared__ uint32_t deg[kDegRanks];
   __shared__ uint32_t rk[kDegRanks];    // rank of sorted slot t
   __shared__ uint32_t wsum[kDegThreads / kWave];
   __shared__ uint32_t wsum2[kDegThreads / kWave];
   const uint64_t w = color_weight(round_key(st->seed, st->round), 0, ctx.ring);
-  uint32_t P = 1;
-  while (P < D) P <<= 1;
-  for (uint32_t t = threadIdx.x; t < P; t += kDegThreads) {
-    if (t < D) {
-      const uint32_t g = d.dlist[t];
-      deg[t] = g;
-      key[t] = mul_int_q(g, w, ctx.ring);
-    } else {
-      deg[t] = 0xFFFFFFFFu;
-      key[t] = ~0ull;
-    }
+  // sorted by the levels of small_sort (a bitonic network of up to 4096 keys
+  // is 78 barriers: R-MAT 20, 36 us)
+  const int lshift = ctx.ring ? 0 : 3;
+  for (uint32_t t = threadIdx.x; t < D; t += kDegThreads) {
+    key[t] = mul_int_q(d.dlist[t], w, ctx.ring) << lshift;
+    L.node[t] = (uint16_t)t;
+    L.seg[t] = 0;
+  }
+  if (threadIdx.x == 0) {
+    L.slen[0] = (uint16_t)D;
+    L.used[0] = 0;
   }
   __syncthreads();
-  for (uint32_t kk = 2; kk <= P; kk <<= 1)
-    for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-      for (uint32_t i = threadIdx.x; i < P; i += kDegThreads) {
-        const uint32_t l = i ^ j;
-        if (l > i) {
-          const bool asc = (i & kk) == 0;
-          const unsigned long long a = key[i], b = key[l];
-          // ties broken by degree so the order is total
-          const bool gt = a > b || (a == b && deg[i] > deg[l]);
-          if (gt == asc) {
-            key[i] = b;
-            key[l] = a;
-            const uint32_t tv = deg[i];
-            deg[i] = deg[l];
-            deg[l] = tv;
-          }
-        }
-      }
-      __syncthreads();
-    }
+  small_sort(L, D);
+  for (uint32_t t = threadIdx.x; t < D; t += kDegThreads) deg[t] = d.dlist[L.node[t]];
+  __syncthreads();
   // rank of slot t = distinct keys before it (block scan of "new key" flags)
   constexpr uint32_t kPer = kDegRanks / kDegThreads;
   const uint32_t t0 = threadIdx.x * kPer;

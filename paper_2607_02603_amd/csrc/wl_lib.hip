@@ -937,11 +937,11 @@ struct Session {
         entries = host.live_entries;  // counted when the live classes were set up
       } else {
         if (live_mode)
-          hipLaunchKernelGGL(k_live_count, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock), 0, s,
-                             ctx, 0);
+          hipLaunchKernelGGL(k_live_count, dim3(grid_for(L.n, 4 * kBlock, 1024)), dim3(kBlock), 0,
+                             s, ctx, 0);
         else
-          hipLaunchKernelGGL(k_count_active<RP>, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock),
-                             0, s, ctx);
+          hipLaunchKernelGGL(k_count_active<RP>, dim3(grid_for(L.n, 4 * kBlock, 1024)),
+                             dim3(kBlock), 0, s, ctx);
         HIP_LAUNCH_CHECK();
         if (int r = pull()) return r;
         entries = host.act_entries;
@@ -1314,8 +1314,12 @@ struct Session {
                          s, ctx, kImgUniform, 1);
     timed_spmv(host.round, true, kImgUniform, [&] {
       hipLaunchKernelGGL(k_deg_clear, dim3(gd), dim3(kBlock), 0, s, ctx, d, maxd);
-      hipLaunchKernelGGL(k_deg_hist<RP64>, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock), 0,
-                         s, ctx, d);
+      // every workgroup ends by adding its counts to the same few counters
+      // (R-MAT 22: 70 us with 4096 workgroups, 23 with 512); larger graphs need
+      // more loads in flight (R-MAT 27: 633 us with 512, 599 with 1024)
+      hipLaunchKernelGGL(k_deg_hist<RP64>,
+                         dim3(grid_for(L.n, kDegStep * kBlock, L.n < (1ull << 24) ? 512 : 1024)),
+                         dim3(kBlock), 0, s, ctx, d);
     });
     hipLaunchKernelGGL(k_deg_list, dim3(gd), dim3(kBlock), 0, s, ctx, d, maxd);
     hipLaunchKernelGGL(k_deg_ranks, dim3(1), dim3(kDegThreads), 0, s, ctx, d);

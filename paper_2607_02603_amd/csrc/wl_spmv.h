@@ -62,32 +62,34 @@ __global__ void __launch_bounds__(kBlock) k_bins_count(Ctx ctx) {
     if (cnt[b]) atomicAdd(&sh[b], cnt[b]);
   atomicMax(&smx, (uint32_t)(mx < 0xFFFFFFFFull ? mx : 0xFFFFFFFFull));
   __syncthreads();
-  if (threadIdx.x == 0 && smx) atomicMax(&ctx.st->max_deg, smx);
+  // (k_bins_scan takes the largest; an atomic per block on one address costs
+  // more than the rest of this kernel on a graph of 10^6 rows)
+  if (threadIdx.x == 0) ctx.scan_part[blockIdx.x] = smx;
   if (threadIdx.x < kNumBins)
     ctx.bin_part[threadIdx.x * gridDim.x + blockIdx.x] = sh[threadIdx.x];
 }
 
-// One block: exclusive scan of the per-block bin counts, bin totals/starts.
+// One block: exclusive scan of the per-block bin counts, bin totals/starts,
+// and the longest row.
 __global__ void __launch_bounds__(kBlock) k_bins_scan(Ctx ctx, uint32_t nblk) {
+  static_assert(kScanBlocks <= 4 * kBlock, "one block scan per bin");
   __shared__ uint32_t sh[kBlock / kWave];
+  __shared__ uint32_t smx;
+  if (threadIdx.x == 0) smx = 0;
+  __syncthreads();
+  uint32_t mx = 0;
+  for (uint32_t i = threadIdx.x; i < nblk; i += kBlock) mx = max(mx, ctx.scan_part[i]);
+  atomicMax(&smx, mx);
   uint32_t start = 0;
   for (int b = 0; b < kNumBins; ++b) {
-    uint32_t carry = 0;
-    uint32_t* part = ctx.bin_part + b * nblk;
-    for (uint32_t base = 0; base < nblk; base += kBlock) {
-      uint32_t i = base + threadIdx.x;
-      uint32_t v = i < nblk ? part[i] : 0;
-      uint32_t tot;
-      uint32_t ex = block_excl_scan(v, sh, &tot);
-      if (i < nblk) part[i] = carry + ex;
-      carry += tot;
-    }
+    const uint32_t carry = block_scan_small(ctx.bin_part + b * nblk, nblk, sh);
     if (threadIdx.x == 0) {
       ctx.st->bin_cnt[b] = carry;
       ctx.st->bin_start[b] = start;
     }
     start += carry;
   }
+  if (threadIdx.x == 0) ctx.st->max_deg = smx;  // the scans' barriers lie between
 }
 
 // HEAVY: only the heavy rows' list (bin 3) is written (the incremental
@@ -517,10 +519,19 @@ __global__ void __launch_bounds__(kBlock) k_live_count(Ctx ctx, int work) {
   if (st->done) return;
   const uint32_t nl = st->nl;
   unsigned long long rows = 0, ents = 0;
-  for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < nl; q += gridDim.x * kBlock) {
-    const uint32_t l = ctx.rl[q];
-    rows += l ? 1 : 0;
-    ents += l;
+  // four positions per thread and step, loaded together: few workgroups keep
+  // the loads in flight, and each ends in one atomic on the same address
+  constexpr uint32_t kStep = 4;
+  const uint64_t stride = (uint64_t)gridDim.x * kBlock * kStep;
+  for (uint64_t q0 = (uint64_t)blockIdx.x * kBlock * kStep + threadIdx.x; q0 < nl; q0 += stride) {
+    uint32_t l[kStep];
+#pragma unroll
+    for (uint32_t u = 0; u < kStep; ++u) l[u] = q0 + u * kBlock < nl ? ctx.rl[q0 + u * kBlock] : 0u;
+#pragma unroll
+    for (uint32_t u = 0; u < kStep; ++u) {
+      rows += l[u] ? 1 : 0;
+      ents += l[u];
+    }
   }
   __shared__ unsigned long long sr[kBlock], se[kBlock];
   sr[threadIdx.x] = rows;
@@ -616,8 +627,18 @@ template <typename RP>
 __global__ void __launch_bounds__(kBlock) k_count_active(Ctx ctx) {
   const RP* rp = rowptr<RP>(ctx);
   unsigned long long ents = 0;
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ctx.n; i += gridDim.x * kBlock)
-    if (ctx.act[i]) ents += rp[i + 1] - rp[i];
+  constexpr uint32_t kStep = 4;  // as in k_live_count
+  const uint64_t stride = (uint64_t)gridDim.x * kBlock * kStep;
+  for (uint64_t i0 = (uint64_t)blockIdx.x * kBlock * kStep + threadIdx.x; i0 < ctx.n; i0 += stride) {
+    uint64_t l[kStep];
+#pragma unroll
+    for (uint32_t u = 0; u < kStep; ++u) {
+      const uint64_t i = i0 + u * kBlock;
+      l[u] = i < ctx.n && ctx.act[i] ? (uint64_t)(rp[i + 1] - rp[i]) : 0ull;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kStep; ++u) ents += l[u];
+  }
   __shared__ unsigned long long se[kBlock];
   se[threadIdx.x] = ents;
   __syncthreads();
