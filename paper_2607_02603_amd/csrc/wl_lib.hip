@@ -163,7 +163,7 @@ Layout make_layout(uint64_t n, uint64_t nnz, bool in_core = true) {
 // are relative to its start.
 struct PbLayout {
   bool ok = false;
-  uint32_t levels = 0, shift1 = 0, nb1 = 0, nfine = 0, fbits = 0;
+  uint32_t levels = 0, half = 0, shift1 = 0, nb1 = 0, nfine = 0, fbits = 0;
   uint64_t ntiles1 = 0;
   uint64_t cnt = 0, bstart1 = 0, bstartf = 0, rec1 = 0, rec2 = 0, tile_row = 0,
            tile2_off = 0, cur1 = 0, cur2 = 0, slice_off = 0, mslice_off = 0, mlist = 0,
@@ -179,6 +179,13 @@ PbLayout make_pb_layout(uint64_t n, uint64_t nnz) {
   if (nf <= kPbMaxBins) {
     P.levels = 1;
     P.shift1 = kPbFineShift;
+  } else if (nf <= 2 * kPbMaxBins) {
+    // pass 1 writes bins of two fine bins, and pass 3 reads such a bin once
+    // for each half: one more read of the records instead of pass 2's read
+    // and write (R-MAT 22, 512 fine bins: the call 0.23 ms shorter)
+    P.levels = 1;
+    P.half = 1;
+    P.shift1 = kPbFineShift + 1;
   } else {
     uint32_t fb = 0;
     while (((nf + (1ull << fb) - 1) >> fb) > kPbMaxBins) ++fb;
@@ -191,7 +198,8 @@ PbLayout make_pb_layout(uint64_t n, uint64_t nnz) {
   P.ntiles1 = (nnz + kPbTile - 1) / kPbTile;
   // slices of the bins cut into several: each holds more than kPbSlice
   // records, so together fewer than 2 * nnz / kPbSlice
-  const uint64_t mslots = 2 * ((nnz + kPbSlice - 1) / kPbSlice) + 1;
+  // (twice as many where both halves of a bin read its slices)
+  const uint64_t mslots = (2ull << P.half) * nnz / kPbSlice + 1;
   uint64_t o = 0;
   auto take = [&](uint64_t bytes) {
     uint64_t at = o;
@@ -984,6 +992,9 @@ struct Session {
         hipLaunchKernelGGL((k_pb_accum<RP, true>), ga, dim3(kPbAccThreads), 0, s, ctx, pb);
       else
         hipLaunchKernelGGL((k_pb_accum<RP, false>), ga, dim3(kPbAccThreads), 0, s, ctx, pb);
+      if (P.half)
+        hipLaunchKernelGGL(k_pb_check_halves, dim3(grid_for(P.nfine)), dim3(kBlock), 0, s, ctx,
+                           pb);
       if (pbc.nmulti)
         hipLaunchKernelGGL(k_pb_combine,
                            dim3(grid_for((uint64_t)pbc.nmulti * kPbFineRows, kBlock, 8192)),
@@ -1820,6 +1831,7 @@ int open_session(Session& S, const wl_csr* g, uint32_t* colors, void* ws,
       uint8_t* B = (uint8_t*)ws + S.L.total;
       PbCtx& p = S.pb;
       p.levels = S.P.levels;
+      p.half = S.P.half;
       p.shift1 = S.P.shift1;
       p.nb1 = S.P.nb1;
       p.nfine = S.P.nfine;

@@ -10,8 +10,8 @@
 //           turns them into records (destination row inside its bin, colour
 //           of the source row), counting-sorts them by bin in LDS and writes
 //           one run per bin, reserved with an atomic on the bin's cursor;
-//   pass 2  only when there are more than kPbMaxBins fine bins: pass 1 used
-//           coarse bins of 2^fbits fine bins each; every coarse bin is split
+//   pass 2  only when there are more than 2 * kPbMaxBins fine bins: pass 1
+//           used coarse bins of 2^fbits fine bins each; every coarse bin is split
 //           into its fine bins the same way (run offsets from atomics), one
 //           tile of kPbTile2 records per workgroup, neighbouring workgroups
 //           on different coarse bins so that their reservations on the
@@ -21,6 +21,14 @@
 //           records into per-row accumulators in LDS; single-slice bins
 //           write z, the partial sums of the others are added by a last
 //           kernel.
+// Between kPbMaxBins and 2 * kPbMaxBins fine bins, pass 1 writes bins of two
+// fine bins, there is no pass 2, and pass 3 reads such a bin once for each of
+// its halves, passing over the other half's records.  That is one more read of
+// 4 B per entry in place of pass 2's read and write and its LDS sort.  Call
+// with certificate on R-MAT 22 of factor 16 (512 fine bins): 2.84 -> 2.61 ms;
+// 4 M nodes in degree order (489 fine bins): 3.16 -> 3.05 ms.  The line is at
+// two halves: each further one is another read, and pass 2 is three passes
+// over the records (read, write, and pass 3's read).
 // For symmetric A, the records bound for rows [a, b) number rp[b] - rp[a],
 // so every bin occupies the entry range of its rows in the CSR layout.  The
 // accumulators are exact (two 64-bit sums of the 32-bit halves of canonical
@@ -54,7 +62,8 @@ struct PbCounts {
 };
 
 struct PbCtx {
-  uint32_t levels;     // 1: pass 1 writes fine bins; 2: coarse bins, then pass 2
+  uint32_t levels;     // 1: pass 3 reads pass 1's bins; 2: coarse bins, then pass 2
+  uint32_t half;       // 1 (levels == 1): a pass-1 bin holds two fine bins
   uint32_t shift1;     // log2 of the rows of a pass-1 bin
   uint32_t nb1;        // pass-1 bins
   uint32_t nfine;      // fine bins
@@ -166,7 +175,9 @@ __global__ void __launch_bounds__(kPbThreads) k_pb_lists(Ctx ctx, PbCtx pb) {
     const uint32_t f = base + threadIdx.x;
     uint32_t ns = 0;
     if (f < pb.nfine) {
-      const uint64_t sz = pb.bstartf[f + 1] - pb.bstartf[f];
+      // the records that the fine bin's items read
+      const uint64_t sz = pb.half ? pb.bstart1[(f >> 1) + 1] - pb.bstart1[f >> 1]
+                                  : pb.bstartf[f + 1] - pb.bstartf[f];
       ns = sz <= kPbSlice ? 1u : (uint32_t)((sz + kPbSlice - 1) / kPbSlice);
     }
     uint32_t tot, mtot, ntot;
@@ -281,8 +292,8 @@ __global__ void __launch_bounds__(kPb1Threads, 4) k_pb_scatter1(Ctx ctx, PbCtx p
   const uint32_t mask1 = (1u << pb.shift1) - 1;
   const bool two = pb.levels == 2;
   uint32_t* out = two ? pb.rec1 : pb.rec2;
-  unsigned long long* cur = two ? pb.cur1 : pb.cur2;
-  const uint64_t* bstart = two ? pb.bstart1 : pb.bstartf;
+  unsigned long long* cur = two || pb.half ? pb.cur1 : pb.cur2;
+  const uint64_t* bstart = two || pb.half ? pb.bstart1 : pb.bstartf;
   const uint4* col4 = (const uint4*)ctx.col;
   for (uint64_t t = blockIdx.x; t < pb.ntiles1; t += gridDim.x) {
     const uint64_t e0 = t * kPbTile, e1 = min(ctx.nnz, e0 + kPbTile);
@@ -570,8 +581,11 @@ __global__ void __launch_bounds__(kPbAccThreads) k_pb_accum(Ctx ctx, PbCtx pb) {
     const uint32_t f = lo;
     const uint32_t q = t - pb.slice_off[f];
     const uint32_t ns = pb.slice_off[f + 1] - pb.slice_off[f];
-    const uint64_t b1 = pb.bstartf[f + 1];
-    const uint64_t a = pb.bstartf[f] + (uint64_t)q * kPbSlice;
+    const uint64_t b1 = pb.half ? pb.bstart1[(f >> 1) + 1] : pb.bstartf[f + 1];
+    const uint64_t a = (pb.half ? pb.bstart1[f >> 1] : pb.bstartf[f]) + (uint64_t)q * kPbSlice;
+    // the records of the other half of the bin are passed over
+    const uint32_t mine = pb.half ? f & 1u : 0u, halves = pb.half;
+    uint32_t seen = 0;
     const uint64_t e = ns == 1 ? b1 : min(b1, a + kPbSlice);
     for (uint32_t r = threadIdx.x; r < kPbFineRows; r += kPbAccThreads) {
       acc[r] = 0;
@@ -599,7 +613,11 @@ __global__ void __launch_bounds__(kPbAccThreads) k_pb_accum(Ctx ctx, PbCtx pb) {
       }
 #pragma unroll
       for (uint32_t u = 0; u < kU; ++u) {
-        const bool ok = p0 + u * kPbAccThreads + threadIdx.x < e;
+        bool ok = p0 + u * kPbAccThreads + threadIdx.x < e;
+        if (halves) {
+          ok = ok && (((rv[u] >> pb.cbits) >> kPbFineShift) & 1u) == mine;
+          seen += ok ? 1u : 0u;
+        }
         const uint32_t local = (rv[u] >> pb.cbits) & (kPbFineRows - 1);
         const uint64_t w =
             ok ? (TBL ? wtab[rv[u] & cmask] : color_weight(key, rv[u] & cmask, ctx.ring))
@@ -626,6 +644,12 @@ __global__ void __launch_bounds__(kPbAccThreads) k_pb_accum(Ctx ctx, PbCtx pb) {
         }
       }
     }
+    if (halves) {
+      // the fine bin's entry count against the records found for it (pass 1
+      // checks the counts of whole bins only); cur2 starts at its first entry
+      for (int off = kWave / 2; off > 0; off >>= 1) seen += __shfl_xor(seen, off, kWave);
+      if (lane_id() == 0 && seen) atomicAdd(&pb.cur2[f], (unsigned long long)seen);
+    }
     __syncthreads();
     const uint64_t row0 = (uint64_t)f << kPbFineShift;
     const uint32_t nrows = (uint32_t)min((uint64_t)kPbFineRows, (uint64_t)ctx.n - row0);
@@ -644,6 +668,14 @@ __global__ void __launch_bounds__(kPbAccThreads) k_pb_accum(Ctx ctx, PbCtx pb) {
     }
     __syncthreads();
   }
+}
+
+// Bins of two halves: the records found for each fine bin are its entries,
+// or A is not symmetric.
+__global__ void __launch_bounds__(kBlock) k_pb_check_halves(Ctx ctx, PbCtx pb) {
+  if (ctx.st->done) return;
+  for (uint32_t f = blockIdx.x * kBlock + threadIdx.x; f < pb.nfine; f += gridDim.x * kBlock)
+    if (pb.cur2[f] != pb.bstartf[f + 1]) atomicOr(&ctx.st->err, kErrNotSymmetric);
 }
 
 // Bins with several slices: z = sum of the partial images.

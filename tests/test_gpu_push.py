@@ -118,17 +118,33 @@ def test_two_scatter_passes(force_pb):
     _exact(g.row_ptr, g.col, seed=2)
 
 
-@pytest.mark.parametrize("hubs", [9000, 40000])
-def test_two_scatter_passes_with_one_large_bin(force_pb, hubs):
-    # node ids in degree order: nearly all entries in the first coarse bin, so
-    # that pass 2 takes its tiles in permuted order; the last bin is cut short
-    rng = np.random.default_rng(hubs)
-    n = 256 * 8192 + 12345
-    u = np.concatenate([rng.integers(0, hubs, 60000), rng.integers(0, n, 4000)])
-    v = np.concatenate([rng.integers(0, hubs, 60000), rng.integers(0, n, 4000)])
+@pytest.mark.parametrize("bins", [256, 511, 512])
+@pytest.mark.parametrize("hubs", [9000, 0])
+def test_bins_beyond_one_pass(force_pb, bins, hubs):
+    # a few rows beyond 256, 511 and 512 fine bins of 8192 rows: pass-1 bins of
+    # two halves up to 512, two scatter passes beyond; entries spread over all
+    # bins, or (node ids in degree order) nearly all in the first one, so that
+    # pass 2 takes its tiles in permuted order
+    rng = np.random.default_rng(bins + hubs)
+    n = bins * 8192 + 1234
+    u = np.concatenate([rng.integers(0, hubs or n, 60000), rng.integers(0, n, 4000)])
+    v = np.concatenate([rng.integers(0, hubs or n, 60000), rng.integers(0, n, 4000)])
     g = inputs.csr_from_edges(n, u, v)
-    _say(f"skewed n={n} nnz={g.nnz}")
+    _say(f"n={n} nnz={g.nnz}")
     _exact(g.row_ptr, g.col, seed=4)
+
+
+def test_asymmetry_inside_a_bin_of_two_halves(force_pb):
+    # one entry moved to the other half of its pass-1 bin: the bin's count is
+    # right, its halves' are not
+    rng = np.random.default_rng(8)
+    n = 300 * 8192
+    g = inputs.csr_from_edges(n, rng.integers(0, n, 30000), rng.integers(0, n, 30000))
+    col = g.col.copy()
+    col[100] ^= 8192
+    with pytest.raises(wl.WlError) as e:
+        wl.wl_stable_coloring(_sym_graph(g.row_ptr, col))
+    assert e.value.code == wl.WL_EINVAL
 
 
 def test_refine_round_each_round(force_pb):
