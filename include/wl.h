@@ -88,7 +88,7 @@ extern "C" {
  * then compute A w by routing each row's value to its neighbours through
  * LDS-sized bins (streaming passes) instead of one random read per entry;
  * this needs the larger workspace wl_workspace_size() reports for such a
- * graph (about 8 bytes more per entry) and is skipped when the workspace is
+ * graph (4 to 8 bytes more per entry) and is skipped when the workspace is
  * smaller.  A graph flagged symmetric that is not is reported as WL_EINVAL
  * when the library notices (it checks the entry counts per bin of rows;
  * results are defined only for correctly flagged graphs). */
@@ -369,7 +369,7 @@ int wl_stats_get(wl_stats *out);
  *   WL_GRAPH=1           replay the device-driven rounds from a HIP graph.
  *   WL_NT_STREAM=1       non-temporal loads of the column indices.
  *   WL_SORT_FIX=n        largest mixed bucket the counting sorts of the
- *                        segments of 65 to 2048 nodes fix by insertion
+ *                        segments of 65 to 2048 nodes rank by pairs
  *                        (default 32; 0 sends every segment with one to the
  *                        sorting networks).
  *   WL_CHAIN_SPINS=n     polls a chained scan of the incremental rounds

@@ -148,7 +148,7 @@ struct Ctx {
   uint32_t ring;       // 0: image in F_p (p = 2^61 - 1); 1: in Z/2^64 (wl_device.h)
   int nt_stream;       // stream col_idx with non-temporal loads
   int key_bits;        // bits of a sort key that may differ inside a segment (61, 64, or fewer)
-  uint32_t cs_fix;     // largest mixed bucket the small-segment sort fixes by insertion
+  uint32_t cs_fix;     // largest mixed bucket the counting sorts rank by pairs
   uint32_t chain_spins;  // polls a chained scan waits for an earlier chunk before it gives up
   // Batch mode (Algorithm 2): the rows are nodes [ext_lo, ext_lo + n) of a
   // larger graph; a column outside that range is a node frozen as its own

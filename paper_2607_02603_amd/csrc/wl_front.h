@@ -788,7 +788,7 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
 // Workgroups [0, kFrontBig) take the classes with more than kFrontWave marked
 // members, one after the other, the rest one class per wave, so that the two
 // kinds run beside each other.  Bound by chains of about a dozen dependent
-// accesses; 25 us a round on the 1024 x 1024 grid, of 48 for the round (a
+// accesses; 20 us a round on the 1024 x 1024 grid, of 42 for the round (a
 // full round: 145).
 template <bool RP64, bool W>
 __global__ void __launch_bounds__(kSmallThreads) k_front_split(Ctx ctx, FrontCtx F, uint32_t i) {

@@ -977,15 +977,19 @@ struct Session {
                          dim3(kPb1Threads), 0, s, ctx, pb);
       if (P.levels == 2) {
         // The bins in turn, a block for every tile of the largest one in each:
-        // best while the bins are about equal (R-MAT 27: 6.5 ms, with permuted
+        // best while the bins are about equal (R-MAT 27: 6.6 ms, with permuted
         // tiles 8.2).  Where the node order follows the degrees one bin holds
         // a large part of the entries and nearly all those blocks are empty
-        // (Chung-Lu, 4e6 nodes: 0.79 ms, with permuted tiles 0.36).
+        // (Chung-Lu, 4e6 nodes, while it had two passes: 0.79 ms, with
+        // permuted tiles 0.36).
         const uint64_t turns = (uint64_t)pbc.maxtiles2 * P.nb1;
         const bool by_bin = turns <= 2ull * pbc.ntiles2;
-        hipLaunchKernelGGL(k_pb_scatter2,
-                           dim3(std::max<uint32_t>(1, by_bin ? (uint32_t)turns : pbc.ntiles2)),
-                           dim3(kPbThreads), 0, s, ctx, pb, by_bin ? 1 : 0);
+        if (by_bin)
+          hipLaunchKernelGGL((k_pb_scatter2<true>), dim3(std::max<uint32_t>(1, (uint32_t)turns)),
+                             dim3(kPbThreads), 0, s, ctx, pb);
+        else
+          hipLaunchKernelGGL((k_pb_scatter2<false>), dim3(std::max<uint32_t>(1, pbc.ntiles2)),
+                             dim3(kPbThreads), 0, s, ctx, pb);
       }
       const dim3 ga(std::max<uint32_t>(1, std::min<uint32_t>(pbc.nslices, 2048)));
       if (host.k <= kPbTableMax)
@@ -1741,8 +1745,8 @@ struct Session {
   }
 
   // A graph that one workgroup's LDS holds goes through wl_small.h whole: the
-  // general path takes 0.6 ms or more for any graph, this one 0.07 ms for
-  // 1500 nodes and 12,000 entries.  The bounds are the LDS (nodes) and where
+  // general path took 0.69 ms for 1500 nodes and 12,000 entries (0.43 ms for
+  // 20,000 nodes and 160,000 entries), this one 0.07 ms.  The bounds are the LDS (nodes) and where
   // one compute unit's loads of the columns cost as much as the general
   // path's launches (entries).  WL_SMALL=0, the tuning variables of the
   // general path, validation and the diagnostics (which describe its image
