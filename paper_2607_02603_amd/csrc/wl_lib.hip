@@ -1515,6 +1515,7 @@ struct Session {
 
   // Queues rounds base .. base + count - 1 (count even) without a read-back.
   int launch_async_rounds(uint32_t base, uint32_t count) {
+    deg_pos_fresh = false;  // it speaks of round base only
     round_passes = async_pass_count();
     if (!use_graph) {
       for (uint32_t i = 0; i < count; ++i) round_live_async(base + i);

@@ -147,3 +147,20 @@ def _seed_for_weight(w, rnd, b):
     key = (unmix(w) - (b + 1) * G) & M
     s1 = (unmix(key) - (rnd + 1) * G) & M
     return (unmix(s1) - G) & M
+
+
+def test_full_round_after_device_driven_rounds(monkeypatch):
+    # The positions that the one-colour round records hold for the round after
+    # it only.  With that round device-driven, a later host-driven one (the
+    # full round before frontier rounds) must not take its image from them.
+    # Rows of 17 to 64 entries: no other round keeps the positions up to date.
+    monkeypatch.setenv("WL_HOST_ROUNDS", "1")
+    monkeypatch.setenv("WL_FRONT", "4")
+    monkeypatch.setenv("WL_PB", "force")
+    n0, pend = 9000, 18  # enough nodes for the one-colour round's tables
+    hubs = np.arange(0, n0, 50)
+    u = np.concatenate([np.arange(n0 - 1), np.repeat(hubs, pend)])
+    v = np.concatenate([np.arange(1, n0), n0 + np.arange(hubs.size * pend)])
+    g = _csr(n0 + hubs.size * pend, u, v)
+    _check(g, seed=3)
+    _check(g, seed=3, ring=True)
