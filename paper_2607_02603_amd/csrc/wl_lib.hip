@@ -1515,7 +1515,9 @@ struct Session {
 
   // Queues rounds base .. base + count - 1 (count even) without a read-back.
   int launch_async_rounds(uint32_t base, uint32_t count) {
-    deg_pos_fresh = false;  // it speaks of round base only
+    // these speak of round 'base' only
+    deg_pos_fresh = false;
+    entries_fresh = false;
     round_passes = async_pass_count();
     if (!use_graph) {
       for (uint32_t i = 0; i < count; ++i) round_live_async(base + i);
@@ -1706,7 +1708,7 @@ struct Session {
     // return at once, but their launches cost more than a read-back (about 45
     // against 20 us), so the groups grow as the square root of the rounds run:
     // 2, 2, 4, 4, 6, 6, ...  Doubled each time, they wasted up to half of all
-    // launches (100 paths of 50 nodes, 25 rounds: 2 + 4 + 8 + 16 queued for 17).
+    // launches (1000 paths of 50 nodes, 25 rounds: 2 + 4 + 8 + 16 queued for 17).
     uint32_t host_rounds = 0, groups = 0;
     uint32_t front_next = front_applies() ? front_from : 0, front_wait = 16;
     while (!host.done) {

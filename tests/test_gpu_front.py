@@ -164,3 +164,37 @@ def test_full_round_after_device_driven_rounds(monkeypatch):
     g = _csr(n0 + hubs.size * pend, u, v)
     _check(g, seed=3)
     _check(g, seed=3, ring=True)
+
+
+def _strip(width, layers, deg):
+    """Layers of 'width' nodes; node j of a layer has the deg / 2 neighbours
+    j .. j + deg / 2 - 1 (mod width) in the next one."""
+    j = np.arange(width)
+    u, v = [], []
+    for t in range(layers - 1):
+        for d in range(deg // 2):
+            u.append(t * width + j)
+            v.append((t + 1) * width + (j + d) % width)
+    return _csr(width * layers, np.concatenate(u), np.concatenate(v))
+
+
+def test_image_of_a_later_full_round_is_chosen_by_its_own_rows():
+    # Labels of their own on the first layer: a layer of 8400 nodes becomes
+    # singletons in every round, more at once than a workgroup splits, so both
+    # attempts at frontier rounds (from round 12 and from round 29 on) go back
+    # at once.  The propagation-blocking image serves rounds 0 to 7 and the
+    # full round of the first attempt, while at least half of the entries feed
+    # rows that need one; by the second attempt fewer do.
+    width, layers = 8400, 50
+    g = _strip(width, layers, 16)
+    assert g.nnz >= 1 << 22
+    init = np.zeros(g.n, np.uint32)
+    init[:width] = 1 + np.arange(width)
+    wl.wl_stats_enable(wl.WL_STATS_TIME)
+    try:
+        _check(g, init=init, seed=1)
+        st = wl.wl_stats_get()
+    finally:
+        wl.wl_stats_enable(0)
+    assert st["rounds"] > 40
+    assert st["pb"]["launches"] == 9
