@@ -156,7 +156,6 @@ __global__ void __launch_bounds__(kBlock) k_front_classes(Ctx ctx, FrontCtx F) {
     F.tc[b] = 0;
     F.ex[b] = 0;
     F.stamp[b] = 0;
-    F.size[b] = 0;  // of classes to come; those of today below
     F.posn[ctx.perm[b]] = b;
     if (b < k) {
       F.start[b] = ctx.cstart[b];
@@ -297,7 +296,9 @@ __global__ void __launch_bounds__(kBlock) k_front_touch(Ctx ctx, FrontCtx F, uin
 // A class split by a whole workgroup: its marked members and their images in
 // LDS, and a hash table of the distinct images (a class with thousands of
 // marked members has a handful as a rule).  With more than kFrontKeys of
-// them the members are ranked by comparing all pairs.
+// them (many paths whose ends differ, say) the members are sorted by image.
+// Ranked by comparing all pairs, as before, a class of 8000 members took 1.5
+// ms a round, ten times a full round of all nodes.
 constexpr uint32_t kFrontKeys = 256, kFrontSlots = 1024, kFrontProbes = 64;
 constexpr uint32_t kFrontBig = 16;       // workgroups for the big classes
 constexpr uint32_t kFrontBigList = kSmallThreads / kFrontBig;
@@ -306,15 +307,15 @@ constexpr uint32_t kFrontPerBlock = 8;   // classes of a workgroup of the others
 struct FrontLds {
   unsigned long long key[kFrontMax];
   uint32_t v[kFrontMax];     // the members; later their places
-  uint16_t slot[kFrontMax];  // hash slot, or the first place of the member's part
-  uint16_t rank[kFrontMax];  // rank inside its part
+  uint16_t slot[kFrontMax];  // hash slot, or (sorted) the member's part
+  uint16_t rank[kFrontMax];  // rank inside its part, or (sorted, by part) its first place
   unsigned long long hkey[kFrontSlots];  // ~0: empty
   uint32_t hcnt[kFrontSlots];
   uint16_t hoff[kFrontSlots];   // first place of the part in the order of the images
   uint16_t hpart[kFrontSlots];  // its index in that order
   uint16_t list[kFrontKeys];    // slots in use
   uint32_t mask[kFrontMax / 32];   // places of the split-off members taken by one of them
-  uint32_t heads[kFrontMax / 32];  // all pairs: first places of the parts
+  uint32_t heads[kFrontMax / 32];  // sorted: first places of the parts
   uint32_t hpre[kFrontMax / 32];   // ... parts before each word
   uint32_t big[kFrontBigList];
   unsigned long long wx[kSmallThreads / kWave];
@@ -488,6 +489,35 @@ __device__ __forceinline__ void front_wave_emit(const FrontCtx& F, uint32_t i, c
   }
 }
 
+// The t marked members of L in order of their images (at most kFrontMax), by a
+// bitonic network over the next power of two: (~0, ~0) pads it, behind every
+// node.
+__device__ __forceinline__ void front_sort(FrontLds& L, uint32_t t) {
+  uint32_t P = 2;
+  while (P < t) P <<= 1;
+  for (uint32_t p = t + threadIdx.x; p < P; p += kSmallThreads) {
+    L.key[p] = ~0ull;
+    L.v[p] = 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  for (uint32_t kk = 2; kk <= P; kk <<= 1) {
+    for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
+      for (uint32_t q = threadIdx.x; q < P / 2; q += kSmallThreads) {
+        const uint32_t a = ((q & ~(j - 1)) << 1) | (q & (j - 1)), b = a | j;
+        const unsigned long long ka = L.key[a], kb = L.key[b];
+        const uint32_t va = L.v[a], vb = L.v[b];
+        if (key_less<true>(kb, vb, ka, va) == ((a & kk) == 0)) {
+          L.key[a] = kb;
+          L.key[b] = ka;
+          L.v[a] = vb;
+          L.v[b] = va;
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
 // A class with more marked members, by the whole workgroup.  The loops over
 // the members are short and stay rolled: unrolled, with the members in
 // registers, the kernel spilled and took 38 us a round on the 1024 x 1024 grid.
@@ -574,7 +604,7 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
     const unsigned long long peers = wave_peers(top, in);
     const int ldr = in ? __ffsll((long long)peers) - 1 : (int)lane;
     const unsigned long long lk = __shfl(key, ldr, kWave);
-    // keys that share the top half only, and the empty mark (Z/2^64): all pairs
+    // keys that share the top half only, and the empty mark (Z/2^64): sorted
     if (in && (lk != key || key == ~0ull)) L.many = 1;
     uint32_t h = top % kFrontSlots, first = 0;
     if (in && (int)lane == ldr && key != ~0ull) {
@@ -638,29 +668,14 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
       }
     }
   } else {
-    for (uint32_t p = threadIdx.x; p < t; p += kSmallThreads) {
-      const unsigned long long k = L.key[p];
-      uint32_t less = 0, eqb = 0, len = 0;
-      for (uint32_t q = 0; q < t; ++q) {
-        const unsigned long long kq = L.key[q];
-        less += kq < k ? 1u : 0u;
-        len += kq == k ? 1u : 0u;
-        eqb += (kq == k && q < p) ? 1u : 0u;
-      }
-      L.slot[p] = (uint16_t)less;
-      L.rank[p] = (uint16_t)eqb;
-      if (eqb == 0) {
-        atomicOr(&L.heads[less >> 5], 1u << (less & 31));
-        if (t < m) {
-          if (k < z0) atomicAdd(&L.lt, 1u);
-          if (k == z0) {
-            L.eq = 1;
-            L.rs = less;
-            L.rlen = len;
-          }
-        } else {
-          atomicMax(&L.best, (len << 16) | (0xFFFFu - less));
-        }
+    front_sort(L, t);
+    // first places of the parts ('p0' is the same for the whole wave)
+    for (uint32_t p0 = wid * kWave; p0 < t; p0 += kSmallThreads) {
+      const uint32_t p = p0 + lane;
+      const unsigned long long h = __ballot(p < t && (p == 0 || L.key[p] != L.key[p - 1]));
+      if (lane == 0) {
+        L.heads[p0 / 32] = (uint32_t)h;
+        L.heads[p0 / 32 + 1] = (uint32_t)(h >> 32);
       }
     }
   }
@@ -674,22 +689,42 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
         b < kFrontMax / 32 ? (uint32_t)__popc(L.heads[b]) : 0u, L.sh, &np);
     if (b < kFrontMax / 32) L.hpre[b] = ex;
     __syncthreads();
+    for (uint32_t p = threadIdx.x; p < t; p += kSmallThreads) {
+      const uint32_t upto = L.heads[p >> 5] & ((2u << (p & 31)) - 1);
+      const uint32_t gi = L.hpre[p >> 5] + __popc(upto) - 1;
+      L.slot[p] = (uint16_t)gi;
+      if ((upto >> (p & 31)) & 1) L.rank[gi] = (uint16_t)p;
+    }
+    __syncthreads();
+    uint32_t longest = 0;
+    for (uint32_t gi = threadIdx.x; gi < np; gi += kSmallThreads) {
+      const uint32_t first = L.rank[gi], end = gi + 1 < np ? L.rank[gi + 1] : t;
+      const unsigned long long k = L.key[first];
+      if (t == m) longest = max(longest, ((end - first) << 16) | (0xFFFFu - gi));
+      else if (k < z0 && (gi + 1 == np || L.key[end] >= z0)) L.lt = gi + 1;
+      if (t < m && k == z0) {
+        L.eq = 1;
+        L.rs = first;
+        L.rlen = end - first;
+      }
+    }
+    for (int off = kWave / 2; off > 0; off >>= 1)
+      longest = max(longest, (uint32_t)__shfl_xor((int)longest, off, kWave));
+    if (lane == 0 && longest) atomicMax(&L.best, longest);
+    __syncthreads();
   }
   const bool eq = L.eq != 0;
   uint32_t rs = L.rs, rlen = L.rlen, ret = L.lt, G = np + (eq ? 0u : 1u);
   if (t == m) {
-    rs = 0xFFFFu - (L.best & 0xFFFFu);
+    rs = 0xFFFFu - (L.best & 0xFFFFu);  // sorted: the part's index
     rlen = L.best >> 16;
     G = np;
   }
   if (G == 1) return;  // the same for every thread
-  // index of the part that starts at place x (hash: by slot)
-  auto part_at = [&](uint32_t x) {
-    return L.hpre[x >> 5] + __popc(L.heads[x >> 5] & ((1u << (x & 31)) - 1));
-  };
   if (t == m) {
     if (many) {
-      ret = part_at(rs);
+      ret = rs;
+      rs = L.rank[ret];
     } else {
       // the thread of the part that stays knows its index
       if (threadIdx.x < np && L.hoff[L.list[threadIdx.x]] == rs)
@@ -728,14 +763,15 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
       bool out = false;
       uint32_t vp = 0, place = 0;
       if (in) {
-        const uint32_t sl = L.slot[p], r = L.rank[p];
-        const uint32_t first = many ? sl : L.hoff[sl];
+        const uint32_t sl = L.slot[p];
+        const uint32_t first = many ? L.rank[sl] : L.hoff[sl];
+        const uint32_t r = many ? p - first : L.rank[p];
         vp = L.v[p];
         out = !(rlen && first == rs);
         if (!out) {
           place = r | 0x80000000u;
         } else {
-          const uint32_t gi = many ? part_at(sl) : L.hpart[sl];
+          const uint32_t gi = many ? sl : L.hpart[sl];
           const uint32_t q = gi + ((t < m && !eq && gi >= ret) ? 1u : 0u);
           const uint32_t id = base + (q < ret ? q : q - 1);
           const uint32_t f = rlen && first > rs ? first - rlen : first;
@@ -744,9 +780,8 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
           F.scls[so + place] = id;
           if (r == 0) {
             F.start[id] = cut + f;
-            if (!many) F.size[id] = L.hcnt[sl];
+            F.size[id] = !many ? L.hcnt[sl] : (sl + 1 < np ? L.rank[sl + 1] : t) - first;
           }
-          if (many) atomicAdd(&F.size[id], 1u);
           // split-off members go to the end of the class; the members found
           // there that stay take the places they leave
           if (t < m && pos4[u] >= cut)

@@ -198,3 +198,29 @@ def test_image_of_a_later_full_round_is_chosen_by_its_own_rows():
         wl.wl_stats_enable(0)
     assert st["rounds"] > 40
     assert st["pb"]["launches"] == 9
+
+
+@pytest.mark.parametrize("front", [None, 2])
+@pytest.mark.parametrize("legs,length", [(255, 40), (256, 40), (257, 40), (2000, 40), (4096, 30),
+                                         (8192, 30)])
+def test_many_images_in_one_class(monkeypatch, legs, length, front):
+    # Leg ends with labels of their own (the first six share one): every round
+    # marks about 'legs' members of the class that the labels have not reached
+    # yet, with as many images and one more (from the tree's side), and from
+    # the meeting of the two sides on all members of a class.  256 images and
+    # 257, from which on the members are sorted; 8192 is the largest class.
+    if front:
+        monkeypatch.setenv("WL_FRONT", str(front))
+    g = _spider(legs, length)
+    ends = np.arange(g.n - legs, g.n)
+    init = np.zeros(g.n, np.uint32)
+    init[ends] = 1 + np.maximum(np.arange(legs) - 5, 0)
+    _check(g, init=init, seed=legs)
+    _check(g, init=init, seed=legs, ring=True)
+    # weights of 0 across the middle of every seventh leg: members that are
+    # marked and have the image of the unmarked ones
+    u = np.repeat(np.arange(g.n), np.diff(np.asarray(g.row_ptr, np.int64)))
+    lo, hi = np.minimum(u, g.col), np.maximum(u, g.col)
+    cut = g.n - legs * (length // 2 + 5)  # first node of a layer
+    wt = np.where((lo < cut) & (hi >= cut) & ((hi - cut) % 7 == 0), 0, 1).astype(np.uint32)
+    _check(g, wt, init=init, seed=legs)
