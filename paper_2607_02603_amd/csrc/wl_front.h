@@ -897,6 +897,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_front_split(Ctx ctx, FrontCtx
 
 // New colours of all classes (their order by colour goes to the other ord
 // array), the class indices of the split-off nodes, the next round's counts.
+// A colour with more than kFrontParts parts is written by the whole workgroup:
+// by its own thread, one class that split into 2000 took 420 us.
+constexpr uint32_t kFrontParts = 16;
 __global__ void __launch_bounds__(kBlock) k_front_apply(Ctx ctx, FrontCtx F, uint32_t i) {
   const FrontRound* cur = &F.r[i & 3];
   FrontRound* nxt = &F.r[(i + 1) & 3];
@@ -919,15 +922,25 @@ __global__ void __launch_bounds__(kBlock) k_front_apply(Ctx ctx, FrontCtx F, uin
     nxt->done = round + 1 >= ctx.st->max_rounds ? 2u : 0u;
   }
   __shared__ uint32_t sh[kBlock / kWave];
+  __shared__ uint32_t wide[kFrontChunk], wide_at[kFrontChunk];  // colours of many parts, old and new
+  __shared__ uint32_t nwide;
   const uint64_t key = round_key(ctx.st->seed, round + 1);
   const uint32_t* ord = F.ord[i & 1];
   uint32_t* ord2 = F.ord[(i + 1) & 1];
   const uint32_t nch = (k + kFrontChunk - 1) / kFrontChunk;
   static_assert(kFrontChunk == 4 * kBlock, "four colours per thread");
   bool zero = false;
+  // part q of class c, whose parts get the colours from nb on
+  auto put = [&](uint32_t q, uint32_t ret, uint32_t c, uint32_t base, uint32_t nb) {
+    const uint32_t id = q == ret ? c : base + (q < ret ? q : q - 1);
+    F.color[id] = nb + q;
+    ord2[nb + q] = id;
+    zero = zero || degenerate_value(color_weight(key, nb + q, ctx.ring), ctx.ring);
+  };
   for (uint32_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
     uint32_t below = 0, pre;
     for (uint32_t b = threadIdx.x; b < ch; b += kBlock) below += F.bsum[b];
+    if (threadIdx.x == 0) nwide = 0;  // the scans' barriers lie before its use
     block_excl_scan(below, sh, &pre);
     const uint32_t b0 = ch * kFrontChunk + 4 * threadIdx.x;
     uint32_t e[4], cc[4], sum = 0;
@@ -945,19 +958,29 @@ __global__ void __launch_bounds__(kBlock) k_front_apply(Ctx ctx, FrontCtx F, uin
       if (b >= k) break;
       const uint32_t nb = b + run;
       uint32_t base = 0, ret = 0;
+      run += e[u];
+      if (e[u] > kFrontParts) {
+        const uint32_t at = atomicAdd(&nwide, 1u);
+        wide[at] = b;
+        wide_at[at] = nb;
+        continue;
+      }
       if (e[u]) {
         base = F.exbase[b];
         ret = F.exret[b];
         F.ex[b] = 0;
       }
-      for (uint32_t q = 0; q <= e[u]; ++q) {
-        const uint32_t id = q == ret ? cc[u] : base + (q < ret ? q : q - 1);
-        F.color[id] = nb + q;
-        ord2[nb + q] = id;
-        zero = zero || degenerate_value(color_weight(key, nb + q, ctx.ring), ctx.ring);
-      }
-      run += e[u];
+      for (uint32_t q = 0; q <= e[u]; ++q) put(q, ret, cc[u], base, nb);
     }
+    __syncthreads();
+    for (uint32_t w = 0; w < nwide; ++w) {
+      const uint32_t b = wide[w], nb = wide_at[w];
+      const uint32_t eb = F.ex[b], cb = ord[b], base = F.exbase[b], ret = F.exret[b];
+      for (uint32_t q = threadIdx.x; q <= eb; q += kBlock) put(q, ret, cb, base, nb);
+      __syncthreads();  // all threads have read its number of parts
+      if (threadIdx.x == 0) F.ex[b] = 0;
+    }
+    __syncthreads();
   }
   if (zero) nxt->overflow = 1;
   for (uint32_t d = blockIdx.x * kBlock + threadIdx.x; d < cur->nd; d += gridDim.x * kBlock)
