@@ -597,6 +597,10 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
   // address go one by one)
   // ('p0' is the same for the whole wave)
   for (uint32_t p0 = wid * kWave; wid < kHashWaves && p0 < t; p0 += kHashWaves * kWave) {
+    // once the members have to be sorted, the table is not needed
+    if (__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(
+            &L.many, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)))
+      break;
     const uint32_t p = p0 + lane;
     const bool in = p < t;
     const unsigned long long key = in ? L.key[p] : 0ull;
