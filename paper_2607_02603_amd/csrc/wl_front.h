@@ -49,6 +49,7 @@ constexpr uint32_t kFrontStable = 4;  // the round found nothing to split
 struct FrontRound {
   uint32_t ns;         // nodes in S
   uint32_t nd;         // classes with marked members
+  uint32_t nbig;       // ... with more than kFrontWave of them
   uint32_t overflow;   // the round must be a full one
   uint32_t k, round, done;
   unsigned long long alloc;  // (classes added << 32) | nodes of the next S
@@ -75,6 +76,7 @@ struct FrontCtx {
   uint32_t* hole;   // scratch, at the class's start
   uint32_t* mover;
   uint32_t* dirty;  // classes with marked members
+  uint32_t* big;    // ... with more than kFrontWave of them
   uint32_t* bsum;   // parts added per chunk of colours
   uint32_t* prev;   // colours before the last full round
   unsigned long long* best;  // per old colour: (size << 32) | ~new colour, its largest part
@@ -289,6 +291,8 @@ __global__ void __launch_bounds__(kBlock) k_front_touch(Ctx ctx, FrontCtx F, uin
       const bool new_class = fresh && slot == 0;
       const uint32_t at = wave_append(new_class, &cur->nd);
       if (new_class) F.dirty[at] = c;
+      // the member that makes it a class for a workgroup
+      if (fresh && slot == kFrontWave) F.big[atomicAdd(&cur->nbig, 1u)] = c;
     }
   }
 }
@@ -300,8 +304,7 @@ __global__ void __launch_bounds__(kBlock) k_front_touch(Ctx ctx, FrontCtx F, uin
 // Ranked by comparing all pairs, as before, a class of 8000 members took 1.5
 // ms a round, ten times a full round of all nodes.
 constexpr uint32_t kFrontKeys = 256, kFrontSlots = 1024, kFrontProbes = 64;
-constexpr uint32_t kFrontBig = 16;       // workgroups for the big classes
-constexpr uint32_t kFrontBigList = kSmallThreads / kFrontBig;
+constexpr uint32_t kFrontBig = 16;       // workgroups for big classes only
 constexpr uint32_t kFrontPerBlock = 8;   // classes of a workgroup of the others (at most 16)
 
 struct FrontLds {
@@ -317,7 +320,6 @@ struct FrontLds {
   uint32_t mask[kFrontMax / 32];   // places of the split-off members taken by one of them
   uint32_t heads[kFrontMax / 32];  // sorted: first places of the parts
   uint32_t hpre[kFrontMax / 32];   // ... parts before each word
-  uint32_t big[kFrontBigList];
   unsigned long long wx[kSmallThreads / kWave];
   uint32_t sh[kSmallThreads / kWave];
   uint32_t rep, lt, eq, best, rs, rlen, nh, nm, base, so, nkeys, many;
@@ -824,11 +826,13 @@ __device__ __forceinline__ void front_split_block(const Ctx& ctx, const FrontCtx
   }
 }
 
-// Workgroups [0, kFrontBig) take the classes with more than kFrontWave marked
-// members, one after the other, the rest one class per wave, so that the two
-// kinds run beside each other.  Bound by chains of about a dozen dependent
-// accesses; 20 us a round on the 1024 x 1024 grid, of 42 for the round (a
-// full round: 145).
+// Workgroups [0, kFrontBig) take classes with more than kFrontWave marked
+// members at once, the others first the rest, one class per wave, so that the
+// two kinds run beside each other, and then the big classes that are left.
+// (With the first kFrontBig alone for all big ones, 1000 of 66 marked members
+// each took 580 us, three times a full round.)  Bound by chains of about a
+// dozen dependent accesses; 20 us a round on the 1024 x 1024 grid, of 42 for
+// the round (a full round: 145).
 template <bool RP64, bool W>
 __global__ void __launch_bounds__(kSmallThreads) k_front_split(Ctx ctx, FrontCtx F, uint32_t i) {
   __shared__ FrontLds L;
@@ -845,9 +849,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_front_split(Ctx ctx, FrontCtx
     // of this launch for 789 classes.
     const uint32_t nb = min(gridDim.x - kFrontBig, (nd + kFrontPerBlock - 1) / kFrontPerBlock);
     const uint32_t blk = blockIdx.x - kFrontBig;
-    if (blk >= nb) return;
     // 'd0' is the same for the whole workgroup
-    for (uint64_t d0 = 0; d0 < nd; d0 += (uint64_t)nb * kWaves) {
+    for (uint64_t d0 = 0; blk < nb && d0 < nd; d0 += (uint64_t)nb * kWaves) {
       const uint64_t d = d0 + (uint64_t)w * nb + blk;
       FrontWave X{};
       if (d < nd) {
@@ -874,29 +877,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_front_split(Ctx ctx, FrontCtx
       if (X.extra) front_wave_emit(F, i, X, cur->k + (uint32_t)(o >> 32), (uint32_t)o);
       __syncthreads();  // wx is read before the next step's write
     }
-    return;
   }
-  // the big classes in list order, dealt to the workgroups in turn ('d0' is
-  // the same for all threads)
-  uint32_t seen = 0;
-  for (uint32_t d0 = 0; d0 < nd; d0 += kSmallThreads) {
-    const uint32_t d = d0 + threadIdx.x;
-    const uint32_t c = d < nd ? F.dirty[d] : 0u;
-    const uint32_t big = d < nd && F.tc[c] > kFrontWave ? 1u : 0u;
-    uint32_t tot;
-    const uint32_t at = seen + pb_block_scan<kSmallThreads>(big, L.sh, &tot);
-    // of the thousand in this step, every kFrontBig-th is this workgroup's
-    const uint32_t mine = (at + kFrontBig - 1 - blockIdx.x) / kFrontBig -
-                          (seen + kFrontBig - 1 - blockIdx.x) / kFrontBig;
-    if (big && at % kFrontBig == blockIdx.x) L.big[mine] = c;
-    const uint32_t nb = (seen + tot + kFrontBig - 1 - blockIdx.x) / kFrontBig -
-                        (seen + kFrontBig - 1 - blockIdx.x) / kFrontBig;
-    __syncthreads();
-    for (uint32_t x = 0; x < nb; ++x)
-      front_split_block<RP64, W>(ctx, F, L, cur, i, L.big[x], rkey);
-    __syncthreads();
-    seen += tot;
-  }
+  const uint32_t nbig = cur->nbig;
+  for (uint32_t x = blockIdx.x; x < nbig; x += gridDim.x)
+    front_split_block<RP64, W>(ctx, F, L, cur, i, F.big[x], rkey);
 }
 
 // New colours of all classes (their order by colour goes to the other ord

@@ -1616,7 +1616,8 @@ struct Session {
     F.scls = c.qcls2;
     F.hole = c.perm_tmp;
     F.mover = c.cstart;
-    F.dirty = c.ids;
+    F.dirty = c.ids;  // at most n / 2 classes of two or more nodes
+    F.big = c.ids + n / 2 + 1;  // at most n / 65
     F.prev = c.rows;  // no row is longer than kHeavyChunk: the list is empty
     return F;
   }

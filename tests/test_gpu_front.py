@@ -224,3 +224,18 @@ def test_many_images_in_one_class(monkeypatch, legs, length, front):
     cut = g.n - legs * (length // 2 + 5)  # first node of a layer
     wt = np.where((lo < cut) & (hi >= cut) & ((hi - cut) % 7 == 0), 0, 1).astype(np.uint32)
     _check(g, wt, init=init, seed=legs)
+
+
+@pytest.mark.parametrize("species,copies,length", [(17, 40, 60), (300, 33, 24)])
+def test_many_classes_for_a_workgroup(monkeypatch, species, copies, length):
+    # Copies of labelled paths: every round marks 2 * copies > 64 members in a
+    # class of every label, in more classes than the workgroups set aside for
+    # such classes, and than there are workgroups.
+    monkeypatch.setenv("WL_FRONT", "1")
+    m = species * copies
+    ids = np.random.default_rng(species).permutation(m * length).reshape(m, length)
+    g = _csr(m * length, ids[:, :-1].ravel(), ids[:, 1:].ravel())
+    init = np.empty(g.n, np.uint32)
+    init[ids] = (np.arange(m) % species)[:, None]
+    _check(g, init=init, seed=species)
+    _check(g, init=init, seed=species, ring=True)
