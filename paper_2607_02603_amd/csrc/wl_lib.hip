@@ -546,7 +546,16 @@ __global__ void __launch_bounds__(kBlock) k_count_colors(Ctx ctx, uint32_t k) {
 // one node each takes them all at once.  R-MAT 22 in about 10^6 classes: one
 // atomic per distinct colour of a wave, peeled one by one, 0.78 ms for the
 // sizes and 0.79 ms for the placement; this 0.37 ms and 0.04 ms.
+// The hash keeps the 64 colours of an aligned group in 64 slots in a row
+// (turned by a hash of the group), which one wave adds with one instruction on
+// two lines: atomics on one line go one by one.  Hashed apart, 16 classes of
+// 10^5 nodes took 288 us, and R-MAT 22 with colours i mod 1000 1240 us.
 constexpr uint32_t kColorTile = 4 * kBlock, kColorSlots = 2 * kColorTile;
+__device__ __forceinline__ uint32_t color_slot(uint32_t c) {
+  const uint32_t g = (c >> 6) * 0x9E3779B1u;
+  static_assert(kColorSlots == 1u << 11, "32 groups of 64 slots");
+  return (g >> 27 << 6) | ((c ^ (g >> 21)) & 63);
+}
 __global__ void __launch_bounds__(kBlock) k_hist_colors(Ctx ctx) {
   __shared__ uint32_t key[kColorSlots];
   __shared__ uint32_t cnt[kColorSlots];
@@ -567,8 +576,7 @@ __global__ void __launch_bounds__(kBlock) k_hist_colors(Ctx ctx) {
 #pragma unroll
     for (uint32_t u = 0; u < kPer; ++u) {
       if (c[u] == 0xFFFFFFFFu) continue;
-      uint32_t s = (c[u] * 0x9E3779B1u) >> 21;
-      static_assert(kColorSlots == 1u << 11, "hash to a slot");
+      uint32_t s = color_slot(c[u]);
       while (true) {
         const uint32_t old = atomicCAS(&key[s], 0xFFFFFFFFu, c[u]);
         if (old == 0xFFFFFFFFu || old == c[u]) break;

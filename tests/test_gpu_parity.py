@@ -224,6 +224,21 @@ def test_refine_round_class_sizes(n, shape):
     assert kg == k2 and np.array_equal(cout.cpu().numpy().view(np.uint32), c2)
 
 
+@pytest.mark.parametrize("step", [1, 63, 64, 65, 2048, 4096])
+@pytest.mark.parametrize("k", [16, 1000, 9001])
+def test_refine_round_colour_spacing(k, step):
+    # colours that the tiles' hash tables keep in a row, and colours whose
+    # distance is that of a group of slots, of a table, or beside them
+    n = 70001
+    g = inputs.csr_from_edges(n, np.arange(n - 1), np.arange(1, n))
+    c = (np.arange(n) % k * step % n).astype(np.uint32)
+    _say(f"k={k} step={step}")
+    dg = _dev_graph(g.row_ptr, g.col)
+    cout, kg = wl.wl_refine_round(dg, torch.from_numpy(c.view(np.int32)).cuda(), n, 11, 1)
+    c2, k2, _ = oracle.refine_round(g.row_ptr, g.col, None, c, n, 11, 1)
+    assert kg == k2 and np.array_equal(cout.cpu().numpy().view(np.uint32), c2)
+
+
 # ---------------------------------------------------------------------------
 # configurations
 # ---------------------------------------------------------------------------
