@@ -292,7 +292,7 @@ def make_graph(name, device):
 
 
 KINDS = ("gather", "pb", "uniform")
-FRONT_FROM = 12  # rounds from which a call may run frontier rounds (include/wl.h)
+FRONT_FROM = 16  # rounds from which a call may run frontier rounds (include/wl.h)
 KIND_KERNELS = {
     "pb": "k_pb_scatter1+k_pb_scatter2+k_pb_accum (propagation-blocking image, one launch "
           "= its three passes)",

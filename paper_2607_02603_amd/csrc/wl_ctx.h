@@ -72,6 +72,7 @@ struct DevState {
   uint32_t npass;       // most radix passes that a round of the call had work for
   uint32_t label_max;   // largest initial label
   uint32_t front_skip;  // the frontier rounds may not go on from this round (wl_front.h)
+  uint32_t front_wide;  // ... would mark too many members of a class
   uint64_t seed;
   // The two big-segment lists: (entries << 32) | tiles.  One 64-bit atomic
   // appends a segment and reserves its tiles, so the tile offsets come out

@@ -142,11 +142,30 @@ __device__ __forceinline__ uint64_t front_image_wave(const Ctx& ctx, const Front
 // images the frontier rounds go on, has a degenerate value.
 __global__ void __launch_bounds__(kBlock) k_front_save(Ctx ctx, uint32_t* prev) {
   DevState* st = ctx.st;
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->front_wide = 0;
   const uint64_t key = round_key(st->seed, st->round);
   for (uint32_t b = blockIdx.x * kBlock + threadIdx.x; b < st->k; b += gridDim.x * kBlock)
     if (degenerate_value(color_weight(key, b, ctx.ring), ctx.ring)) st->front_skip = 1;
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ctx.n; i += gridDim.x * kBlock)
     prev[i] = ctx.c[i];
+}
+
+// After that round: whether two parts of a class that split in it have more
+// than kFrontMax nodes each.  One of them would be in S, and its nodes mark
+// as many members of some class as a rule, which sends the first frontier
+// round back: many copies of the same graph, whose every class is that large.
+// Asked before the change, which costs two full rounds (50,000 paths of 28 to
+// 32 nodes: a call of 14 to 16 rounds took 1.15 times as long).
+__global__ void __launch_bounds__(kBlock) k_front_wide(Ctx ctx) {
+  DevState* st = ctx.st;
+  const uint32_t ns = st->nsub;
+  for (uint32_t g = blockIdx.x * kBlock + threadIdx.x; g < ns; g += gridDim.x * kBlock) {
+    if (ctx.gend[g] - ctx.gstart[g] <= kFrontMax) continue;
+    const uint32_t j = ctx.qcls[ctx.gstart[g]];
+    const uint32_t last = ctx.ids[ctx.loff[j] + ctx.llen[j] - 1];  // of the class's parts
+    for (uint32_t h = g + 1; h <= min(last, g + 256); ++h)
+      if (ctx.gend[h] - ctx.gstart[h] > kFrontMax) st->front_wide = 1;
+  }
 }
 
 // Per class and per node state, from the grouping by colour (perm, cstart).
@@ -251,6 +270,12 @@ __global__ void __launch_bounds__(kBlock) k_front_touch(Ctx ctx, FrontCtx F, uin
     return;
   }
   if (first) *nxt = FrontRound{};
+  // the first round is launched before S is known: with a quarter of the
+  // nodes in it a full round is no dearer
+  if (i == 0 && (uint64_t)cur->ns * 4 > ctx.n) {
+    if (first) cur->overflow = 1;
+    return;
+  }
   const uint32_t nb = ctx.n / kFrontChunk + 1;
   for (uint32_t b = blockIdx.x * kBlock + threadIdx.x; b < nb; b += gridDim.x * kBlock)
     F.bsum[b] = 0;
@@ -991,7 +1016,6 @@ __global__ void __launch_bounds__(kBlock) k_front_exit(Ctx ctx, FrontCtx F, uint
     st->k = r->k;
     st->round = r->round;
     st->done = r->done == 2 ? 2 : 0;
-    st->live_entries = 0;
   }
 }
 

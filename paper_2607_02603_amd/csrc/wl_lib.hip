@@ -622,8 +622,16 @@ __global__ void __launch_bounds__(kBlock) k_position_colors(Ctx ctx) {
 
 constexpr uint32_t kHostRounds = 8;
 // Rounds before frontier rounds are tried: most graphs are stable by then, and
-// the change costs about as much as two full rounds.
-constexpr uint32_t kFrontFrom = 12;
+// the change costs two to three full rounds.  A call that ends right after a
+// change in vain takes about 1.1 times as long (1000 paths of 28 nodes, 14
+// rounds), so the larger graphs, whose rounds cost more than their launches,
+// wait longer (2^18 nodes: a grid of 35 rounds on 4900 nodes gains 10 % from
+// the earlier one, the 1024 x 1024 grid of 512 rounds 2 %).
+constexpr uint32_t kFrontFrom = 12, kFrontFromLarge = 16;
+constexpr uint64_t kFrontLarge = 1ull << 18;
+// Rounds until the next try, doubled whenever fewer frontier rounds ran than
+// make up for the change.
+constexpr uint32_t kFrontWait = 16, kFrontPays = 4;
 constexpr int kAsyncPassesDefault = 2;
 
 int env_int(const char* name, int lo, int hi, int dflt) {
@@ -1643,10 +1651,11 @@ struct Session {
 
   // Runs frontier rounds after the full round that just ended, whose start
   // colours are in F.prev, and returns to the full rounds' state.  *again:
-  // the coming full round only confirms that no class splits.
-  int front_rounds(bool* again, bool* ran) {
+  // the coming full round only confirms that no class splits.  *ran: how many
+  // there were.
+  int front_rounds(bool* again, uint32_t* ran) {
     *again = false;
-    *ran = false;
+    *ran = 0;
     ctx = ctx0;
     const FrontCtx F = front_ctx();
     const uint32_t gn = grid_for(L.n, kBlock, 4096);
@@ -1657,13 +1666,10 @@ struct Session {
     hipLaunchKernelGGL(k_front_seed, dim3(gn), dim3(kBlock), 0, s, ctx, F);
     HIP_LAUNCH_CHECK();
     FrontRound fr{};
-    HIP_TRY(hipMemcpyAsync(&fr, F.r, sizeof fr, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
     const uint32_t lg = host.max_deg <= 4 ? 2 : (host.max_deg <= 8 ? 3 : 4);
-    const uint32_t round0 = fr.round;
+    const uint32_t round0 = host.round;
     uint32_t i = 0, ahead = 8;
-    // with a quarter of the nodes in S a full round is no dearer
-    while ((uint64_t)fr.ns * 4 <= L.n && !fr.done) {
+    while (!fr.done && (uint64_t)fr.ns * 4 <= L.n) {
       for (uint32_t x = 0; x < ahead; ++x, ++i) {
         if (rp64) {
           if (weighted) front_round<true, true>(F, i, lg); else front_round<true, false>(F, i, lg);
@@ -1678,14 +1684,22 @@ struct Session {
       ahead = std::min<uint32_t>(2 * ahead, 64);
     }
     *again = fr.done == kFrontStable;
-    *ran = fr.round > round0;
-    if (sflags & WL_STATS_TIME) stats.gather.launches += fr.round - round0;  // not timed
+    *ran = fr.round - round0;
+    if (sflags & WL_STATS_TIME) stats.gather.launches += *ran;  // not timed
     hipLaunchKernelGGL(k_front_exit, dim3(gn), dim3(kBlock), 0, s, ctx, F, i);
     HIP_LAUNCH_CHECK();
     if (fr.done == 2) return pull();
-    group_by_color(fr.k);
-    hipLaunchKernelGGL(k_position_colors, dim3(gn), dim3(kBlock), 0, s, ctx);
     host.k = fr.k;
+    return rebuild_live();
+  }
+
+  // The live classes again, from the colours: their members about in node
+  // order.
+  int rebuild_live() {
+    ctx = ctx0;
+    group_by_color(host.k);
+    hipLaunchKernelGGL(k_position_colors, dim3(grid_for(L.n, kBlock, 4096)), dim3(kBlock), 0, s,
+                       ctx);
     return build_live_now();
   }
 
@@ -1716,10 +1730,10 @@ struct Session {
     // per group.  Rounds queued past the last one find the state done and
     // return at once, but their launches cost more than a read-back (about 45
     // against 20 us), so the groups grow as the square root of the rounds run:
-    // 2, 2, 4, 4, 6, 6, ...  Doubled each time, they wasted up to half of all
+    // 2, 4, 4, 6, 6, ...  Doubled each time, they wasted up to half of all
     // launches (1000 paths of 50 nodes, 25 rounds: 2 + 4 + 8 + 16 queued for 17).
     uint32_t host_rounds = 0, groups = 0;
-    uint32_t front_next = front_applies() ? front_from : 0, front_wait = 16;
+    uint32_t front_next = front_applies() ? front_from : 0, front_wait = kFrontWait;
     while (!host.done) {
       if (front_next && live_built && host.round >= front_next) {
         // one more full round, from known colours, then frontier rounds for
@@ -1727,15 +1741,28 @@ struct Session {
         hipLaunchKernelGGL(k_front_save, dim3(gn), dim3(kBlock), 0, s, ctx, front_ctx().prev);
         if (int r = round_live()) return r;
         if (host.done) break;
-        bool again = false, ran = false;
-        if (int r = front_rounds(&again, &ran)) return r;
+        if (L.n > 2 * kFrontMax) {
+          hipLaunchKernelGGL(k_front_wide, dim3(live_grid()), dim3(kBlock), 0, s, ctx);
+          HIP_LAUNCH_CHECK();
+          if (int r = pull()) return r;
+        }
+        bool again = false;
+        uint32_t ran = 0;
+        if (!host.front_wide) {
+          if (int r = front_rounds(&again, &ran)) return r;
+        } else if (front_wait > kFrontWait) {
+          // A call this long gets its members in node order back, which the
+          // rounds' sorts mix up (3000 x 3000 grid: image and emit of a full
+          // round 0.66 -> 0.47 ms).
+          if (int r = rebuild_live()) return r;
+        }
         if (again && !host.done) {
           // stable by the frontier's account: a full round has the last word
           if (int r = round_live()) return r;
           front_next = 0;
         } else {
           front_next = host.round + front_wait;
-          if (!ran) front_wait = std::min<uint32_t>(2 * front_wait, 1u << 16);
+          if (ran < kFrontPays) front_wait = std::min<uint32_t>(2 * front_wait, 1u << 16);
         }
         continue;
       }
@@ -1746,7 +1773,7 @@ struct Session {
       }
       if (!live_built)
         if (int r = build_live_now()) return r;
-      const uint32_t ahead = std::min<uint32_t>(2 * (1 + groups / 2), 64);
+      const uint32_t ahead = std::min<uint32_t>(2 * (1 + (groups + 1) / 2), 64);
       ++groups;
       if (int r = launch_async_rounds(host.round, ahead)) return r;
       if (int r = pull()) return r;
@@ -1841,7 +1868,8 @@ int open_session(Session& S, const wl_csr* g, uint32_t* colors, void* ws,
   {
     // the tuning of the device-driven full rounds keeps them the rounds that run
     const bool tuned = getenv("WL_HOST_ROUNDS") || getenv("WL_ASYNC_PASSES") || S.use_graph;
-    S.front_from = (uint32_t)env_int("WL_FRONT", 0, 1 << 30, tuned ? 0 : (int)kFrontFrom);
+    const uint32_t from = g->n < kFrontLarge ? kFrontFrom : kFrontFromLarge;
+    S.front_from = (uint32_t)env_int("WL_FRONT", 0, 1 << 30, tuned ? 0 : (int)from);
   }
   if (wants_pb(g) && S.pb_mode != 0) {
     S.P = make_pb_layout(g->n, g->nnz);

@@ -190,6 +190,7 @@ __global__ void __launch_bounds__(kBlock) k_live_class_vals(Ctx ctx) {
     ctx.gl[b] = live ? 1u : 0u;
     ctx.go[b] = live ? ctx.cstart[b + 1] - ctx.cstart[b] : 0u;
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctx.st->live_entries = 0;
 }
 
 // Members of the live classes in colour order, with their row spans (into

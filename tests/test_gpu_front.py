@@ -181,7 +181,7 @@ def _strip(width, layers, deg):
 def test_image_of_a_later_full_round_is_chosen_by_its_own_rows():
     # Labels of their own on the first layer: a layer of 8400 nodes becomes
     # singletons in every round, more at once than a workgroup splits, so both
-    # attempts at frontier rounds (from round 12 and from round 29 on) go back
+    # attempts at frontier rounds (from round 12 or 16 on, and 17 rounds later) go back
     # at once.  The propagation-blocking image serves rounds 0 to 7 and the
     # full round of the first attempt, while at least half of the entries feed
     # rows that need one; by the second attempt fewer do.
@@ -239,3 +239,14 @@ def test_many_classes_for_a_workgroup(monkeypatch, species, copies, length):
     init[ids] = (np.arange(m) % species)[:, None]
     _check(g, init=init, seed=species)
     _check(g, init=init, seed=species, ring=True)
+
+
+@pytest.mark.parametrize("front", [None, 1])
+@pytest.mark.parametrize("copies", [4096, 4097])
+def test_copies_of_a_path(monkeypatch, copies, front):
+    # every class has 2 * copies nodes: as many as a workgroup splits, and
+    # more, for which the change to frontier rounds is not made
+    if front:
+        monkeypatch.setenv("WL_FRONT", str(front))
+    ids = np.arange(copies * 44).reshape(copies, 44)
+    _check(_csr(ids.size, ids[:, :-1].ravel(), ids[:, 1:].ravel()), seed=copies)
