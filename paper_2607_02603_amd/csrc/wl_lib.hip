@@ -1978,7 +1978,9 @@ int verify_run(const wl_csr* g, const uint32_t* color, uint32_t k, uint8_t* ws,
   if (h.err & kVErrColor) return fail(WL_EINVAL, "a colour is >= k");
   hipLaunchKernelGGL(k_v_multi<K>, dim3(gn), dim3(kBlock), 0, s, v);
   hipLaunchKernelGGL(k_v_bin<K>, dim3(gn), dim3(kBlock), 0, s, v);
-  hipLaunchKernelGGL(k_v_sort_wave<K>, dim3(gn), dim3(kBlock), 0, s, v);
+  const uint32_t per = v_nodes_per_wave(v.n);
+  const uint32_t gw = grid_for(((uint64_t)v.n + per - 1) / per, kBlock / kWave, 4096);
+  hipLaunchKernelGGL(k_v_sort_wave<K>, dim3(gw), dim3(kBlock), 0, s, v, per);
   HIP_LAUNCH_CHECK();
   if (int r = pull()) return r;
   if (h.n_mid)
@@ -1998,7 +2000,7 @@ int verify_run(const wl_csr* g, const uint32_t* color, uint32_t k, uint8_t* ws,
     }
   }
   if constexpr (sizeof(K) == 4)
-    hipLaunchKernelGGL(k_v_compare, dim3(gn), dim3(kBlock), 0, s, v);
+    hipLaunchKernelGGL(k_v_compare, dim3(gw), dim3(kBlock), 0, s, v, per);
   else
     hipLaunchKernelGGL(k_v_compare_w, dim3(gn), dim3(kBlock), 0, s, v);
   HIP_LAUNCH_CHECK();

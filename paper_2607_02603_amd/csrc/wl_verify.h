@@ -180,22 +180,34 @@ __device__ __forceinline__ K group_bitonic(K key, uint32_t lane) {
 constexpr uint32_t kVLane = 8;    // rows sorted by one lane in registers
 constexpr uint32_t kVGroup = 16;  // ... by 16 lanes; longer ones (<= 64) by the wave
 
-// Rows of 1 .. 64 entries.  A wave takes 64 consecutive nodes, one per lane,
+// Nodes that a wave of the row sorts and of the comparison takes: a power of
+// two, 64 where there are enough waves.  With 64 always, the rows that need a
+// whole wave, one after the other, made small regular graphs slower than one
+// wave per node did (2000 nodes of 32 entries: 124 us a call, with 64 nodes
+// per wave 210).
+constexpr uint64_t kVWaves = 8192;
+inline uint32_t v_nodes_per_wave(uint64_t n) {
+  uint32_t per = 1;
+  while (per < (uint32_t)kWave && per * kVWaves < n) per *= 2;
+  return per;
+}
+
+// Rows of 1 .. 64 entries.  A wave takes 'per' consecutive nodes, one per lane,
 // so the colours and row pointers are read coalesced; most nodes of a
 // refined graph are alone in their class or have no entry, and a wave per
 // node spent its time on finding that out (R-MAT 22: 0.56 ms, now 0.04 ms).
 // Rows of at most 8 entries are sorted by their lane (a 19-comparator
 // network), rows of up to 16 four at a time, the others one at a time.
 template <typename K>
-__global__ void __launch_bounds__(kBlock) k_v_sort_wave(VerCtx<K> v) {
+__global__ void __launch_bounds__(kBlock) k_v_sort_wave(VerCtx<K> v, uint32_t per) {
   const uint32_t lane = lane_id();
-  const uint64_t step = (uint64_t)gridDim.x * kBlock;
+  const uint64_t step = (uint64_t)gridDim.x * (kBlock / kWave) * per;
   // 'base' is the same for all lanes of a wave (the shuffles need them all)
-  for (uint64_t base = blockIdx.x * (uint64_t)kBlock + threadIdx.x - lane; base < v.n;
-       base += step) {
+  for (uint64_t base = (blockIdx.x * (uint64_t)(kBlock / kWave) + threadIdx.x / kWave) * per;
+       base < v.n; base += step) {
     const uint64_t i = base + lane;
     uint64_t b = 0, len = 0;
-    if (i < v.n && v.multi[v.color[i]]) {
+    if (lane < per && i < v.n && v.multi[v.color[i]]) {
       b = v_beg(v, (uint32_t)i);
       len = v_beg(v, (uint32_t)i + 1) - b;
     }
@@ -414,19 +426,19 @@ __global__ void __launch_bounds__(kBlock) k_v_hub_finish(VerCtx<K> v, uint64_t k
   }
 }
 
-// Unweighted: every node's sorted list against its representative's, one
-// node per lane (coalesced colours and row pointers; R-MAT 22: 0.21 ms with 16
-// lanes per node, now 0.05 ms); lists of more than kVLane entries are compared by the
-// whole wave, one node after the other.
-__global__ void __launch_bounds__(kBlock) k_v_compare(VerCtx<uint32_t> v) {
+// Unweighted: every node's sorted list against its representative's, one of
+// 'per' nodes per lane (coalesced colours and row pointers; R-MAT 22: 0.21 ms
+// with 16 lanes per node, now 0.05 ms); lists of more than kVLane entries are
+// compared by 16 lanes each, four at a time, those beyond a wave by all lanes.
+__global__ void __launch_bounds__(kBlock) k_v_compare(VerCtx<uint32_t> v, uint32_t per) {
   const uint32_t lane = lane_id();
-  const uint64_t step = (uint64_t)gridDim.x * kBlock;
-  for (uint64_t base = blockIdx.x * (uint64_t)kBlock + threadIdx.x - lane; base < v.n;
-       base += step) {
+  const uint64_t step = (uint64_t)gridDim.x * (kBlock / kWave) * per;
+  for (uint64_t base = (blockIdx.x * (uint64_t)(kBlock / kWave) + threadIdx.x / kWave) * per;
+       base < v.n; base += step) {
     const uint64_t i = base + lane;
     uint64_t bi = 0, li = 0, br = 0;
     bool bad = false;
-    if (i < v.n) {
+    if (lane < per && i < v.n) {
       const uint32_t r = v.rep[v.color[i]];
       if (r != (uint32_t)i) {
         bi = v_beg(v, (uint32_t)i);
@@ -439,7 +451,22 @@ __global__ void __launch_bounds__(kBlock) k_v_compare(VerCtx<uint32_t> v) {
     if (li <= kVLane)
       for (uint32_t t = 0; t < (uint32_t)li; ++t)
         if (v.keys[bi + t] != v.keys[br + t]) bad = true;
-    for (unsigned long long m = __ballot(li > kVLane); m; m &= m - 1) {
+    const uint32_t g = lane / kVGroup, sub = lane % kVGroup;
+    unsigned long long m = __ballot(li > kVLane && li <= (uint64_t)kWave);
+    while (m) {
+      const int l = nth_bit(m, (int)g);
+      const uint64_t gb = __shfl(bi, l & (kWave - 1), kWave);
+      const uint64_t gr = __shfl(br, l & (kWave - 1), kWave);
+      uint64_t gl = __shfl(li, l & (kWave - 1), kWave);
+      if (l == kWave) gl = 0;  // fewer rows left than groups
+#pragma unroll
+      for (uint32_t u = 0; u < kWave / kVGroup; ++u) {
+        const uint32_t t = sub + u * kVGroup;
+        if (t < gl && v.keys[gb + t] != v.keys[gr + t]) bad = true;
+      }
+      for (uint32_t t = 0; t < kWave / kVGroup; ++t) m &= m - 1;
+    }
+    for (m = __ballot(li > (uint64_t)kWave); m; m &= m - 1) {
       const int l = __builtin_ctzll(m);
       const uint64_t wb = read_lane64(bi, l), wl = read_lane64(li, l), wr = read_lane64(br, l);
       for (uint64_t t = lane; t < wl; t += kWave)

@@ -129,6 +129,24 @@ def test_short_rows_every_sort_path(deg, weighted):
         assert _agree(rp, col, wt, c) == (mutate is None)
 
 
+@pytest.mark.parametrize("n,deg", [(n, d) for n in (2, 67, 8191, 8193, 16385)
+                                   for d in (8, 10, 16, 18, 64, 66)] + [(524289, 10)])
+def test_regular_graph_every_share_of_a_wave(n, deg):
+    # one class of equal rows, at the sizes where the nodes per wave change:
+    # one that compares every row, stable, and with one entry of a late row
+    # moved to a node of another class
+    n = max(n, deg + 2)
+    i = np.arange(n)
+    col = (i[:, None] + 1 + np.arange(deg)) % (n - 1)
+    rp = np.arange(n + 1, dtype=np.uint64) * deg
+    c = np.zeros(n, np.uint32)
+    c[n - 1] = 1  # no entry leads to it
+    _say(f"n={n} deg={deg}")
+    assert _agree(rp, col.astype(np.uint32).ravel(), None, c)
+    col[n - 2, deg // 2] = n - 1
+    assert not _agree(rp, col.astype(np.uint32).ravel(), None, c)
+
+
 def test_many_hubs_of_mixed_lengths():
     # one class per length, 3 hubs each: every merge stage runs with rows
     # of different padded lengths side by side
