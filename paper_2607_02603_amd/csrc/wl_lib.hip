@@ -980,6 +980,14 @@ struct Session {
     return WL_OK;
   }
 
+  template <typename RP, bool TBL>
+  void pb_accum(dim3 g) {
+    if (P.half)
+      hipLaunchKernelGGL((k_pb_accum<RP, TBL, true>), g, dim3(kPbAccThreads), 0, s, ctx, pb);
+    else
+      hipLaunchKernelGGL((k_pb_accum<RP, TBL, false>), g, dim3(kPbAccThreads), 0, s, ctx, pb);
+  }
+
   template <typename RP>
   int pb_round() {
     if (!pb_planned)
@@ -1009,9 +1017,9 @@ struct Session {
       }
       const dim3 ga(std::max<uint32_t>(1, std::min<uint32_t>(pbc.nslices, 2048)));
       if (host.k <= kPbTableMax)
-        hipLaunchKernelGGL((k_pb_accum<RP, true>), ga, dim3(kPbAccThreads), 0, s, ctx, pb);
+        pb_accum<RP, true>(ga);
       else
-        hipLaunchKernelGGL((k_pb_accum<RP, false>), ga, dim3(kPbAccThreads), 0, s, ctx, pb);
+        pb_accum<RP, false>(ga);
       if (P.half)
         hipLaunchKernelGGL(k_pb_check_halves, dim3(grid_for(P.nfine)), dim3(kBlock), 0, s, ctx,
                            pb);
