@@ -180,11 +180,12 @@ int wl_stable_coloring_noalloc(const wl_csr *g, const uint32_t *init_color,
  * page-locked staging buffers and copied to the device in chunks of at most
  * 64M entries, on a copy stream of the library's own, while the device
  * computes the images of the previous chunk; the colours, images and the
- * relabel stay in the workspace.  When the entry arrays are page-locked, a
- * round that needs at least 3/4 of the entries copies them all from there,
- * unpacked, and chunks have at most 16M entries.  The rounds, seeds and colour ids are those
- * of wl_stable_coloring: for the same graph, labels and seed both return
- * the same colours, colour count and round count.
+ * relabel stay in the workspace.  When the entry arrays are page-locked and
+ * hold at most 2^33 entries, a round that needs at least 3/4 of them copies
+ * them all from there, unpacked, and chunks have at most 16M entries.  The
+ * rounds, seeds and colour ids are those of wl_stable_coloring: for the same
+ * graph, labels and seed both return the same colours, colour count and round
+ * count.
  *   g_host      host CSR (pageable or page-locked), n < 2^31.
  *   init_host   host labels or NULL (trivial partition).
  *   color_out_host  host, n entries: raw rank ids as from wl_stable_coloring.
