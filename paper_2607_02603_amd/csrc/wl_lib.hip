@@ -385,8 +385,21 @@ int check_graph(const wl_csr* g) {
   return WL_OK;
 }
 
-int fail_nnz(uint64_t nnz) {
-  return fail(WL_EINVAL, "row_ptr[n] does not equal nnz = %llu", (unsigned long long)nnz);
+// row_ptr[n] (device) is not nnz: the error, with what it is.
+int fail_nnz(const uint32_t* rp32, const uint64_t* rp64, uint64_t n, uint64_t nnz,
+             hipStream_t s) {
+  uint64_t last = 0;
+  if (rp64) {
+    HIP_TRY(hipMemcpyAsync(&last, rp64 + n, 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+  } else {
+    uint32_t v = 0;
+    HIP_TRY(hipMemcpyAsync(&v, rp32 + n, 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    last = v;
+  }
+  return fail(WL_EINVAL, "row_ptr[n] = %llu but nnz = %llu", (unsigned long long)last,
+              (unsigned long long)nnz);
 }
 
 // ---------------------------------------------------------------------------
@@ -822,7 +835,7 @@ struct Session {
   // What the device found in the call's arguments before any column or
   // weight was used; after a read-back.
   int input_errors() const {
-    if (host.err & kErrNnz) return fail_nnz(L.nnz);
+    if (host.err & kErrNnz) return fail_nnz(ctx.rp32, ctx.rp64, L.n, L.nnz, s);
     if (host.err & kErrRowSum)
       return fail(WL_EOVERFLOW, "a row sum exceeds 2^32, the bound of arithmetic mod 2^64");
     return WL_OK;
@@ -1982,7 +1995,7 @@ int verify_run(const wl_csr* g, const uint32_t* color, uint32_t k, uint8_t* ws,
   hipLaunchKernelGGL(k_v_rep<K>, dim3(gn), dim3(kBlock), 0, s, v);
   HIP_LAUNCH_CHECK();
   if (int r = pull()) return r;
-  if (h.err & kVErrNnz) return fail_nnz(g->nnz);
+  if (h.err & kVErrNnz) return fail_nnz(v.rp32, v.rp64, v.n, g->nnz, s);
   if (h.err & kVErrColor) return fail(WL_EINVAL, "a colour is >= k");
   hipLaunchKernelGGL(k_v_multi<K>, dim3(gn), dim3(kBlock), 0, s, v);
   hipLaunchKernelGGL(k_v_bin<K>, dim3(gn), dim3(kBlock), 0, s, v);

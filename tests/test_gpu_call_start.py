@@ -40,8 +40,8 @@ def test_row_pointer_that_does_not_end_at_nnz(n, ring):
     col = np.concatenate([g.col, g.col[:5]])
     wt = np.ones(col.size, np.uint32)
     color = torch.zeros(n, dtype=torch.int32, device="cuda")
-    for w in (None, wt):
-        dg = wl.Graph.from_numpy(n, g.row_ptr, col, w, device="cuda")
+    for w, rp_type in ((None, np.uint32), (wt, np.uint32), (None, np.uint64)):
+        dg = wl.Graph.from_numpy(n, np.asarray(g.row_ptr, rp_type), col, w, device="cuda")
         with wl.precision(wl.WL_PRECISION_RING64 if ring else wl.WL_PRECISION_FP):
             for call in (lambda: wl.wl_stable_coloring(dg),
                          lambda: wl.wl_stable_coloring(dg, color),
@@ -51,3 +51,4 @@ def test_row_pointer_that_does_not_end_at_nnz(n, ring):
                 with pytest.raises(wl.WlError) as e:
                     call()
                 assert e.value.code == wl.WL_EINVAL
+                assert f"row_ptr[n] = {g.nnz} but nnz = {col.size}" in str(e.value)
