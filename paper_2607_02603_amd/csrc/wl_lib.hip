@@ -1706,7 +1706,7 @@ struct Session {
     }
     *again = fr.done == kFrontStable;
     *ran = fr.round - round0;
-    if (sflags & WL_STATS_TIME) stats.gather.launches += *ran;  // not timed
+    stats.gather.launches += *ran;  // not timed
     hipLaunchKernelGGL(k_front_exit, dim3(gn), dim3(kBlock), 0, s, ctx, F, i);
     HIP_LAUNCH_CHECK();
     if (fr.done == 2) return pull();

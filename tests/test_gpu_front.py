@@ -250,3 +250,17 @@ def test_copies_of_a_path(monkeypatch, copies, front):
         monkeypatch.setenv("WL_FRONT", str(front))
     ids = np.arange(copies * 44).reshape(copies, 44)
     _check(_csr(ids.size, ids[:, :-1].ravel(), ids[:, 1:].ravel()), seed=copies)
+
+
+@pytest.mark.parametrize("flags", [0, wl.WL_STATS_TIME])
+def test_image_launches_count_every_round(flags):
+    # timed or not, a call has one image launch for every round that ran
+    g = inputs.grid_graph(70, 90)
+    wl.wl_stats_enable(flags)
+    try:
+        _check(g, seed=1)
+        st = wl.wl_stats_get()
+    finally:
+        wl.wl_stats_enable(0)
+    assert st["rounds"] > 40
+    assert sum(st[kd]["launches"] for kd in ("gather", "pb", "uniform")) == st["rounds"]
