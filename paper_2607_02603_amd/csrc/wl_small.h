@@ -249,7 +249,11 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(Ctx ctx, SmallArgs A) {
     }
     return;
   }
-  if (threadIdx.x == 0) L.bad = 0;
+  if (threadIdx.x == 0) {
+    L.bad = 0;
+    L.nmid = 0;
+    L.nlong = 0;
+  }
   for (uint32_t i = threadIdx.x; i <= n; i += kSmallThreads) L.rp[i] = rp_in(i);
   if (LCOL)
     for (uint32_t e = threadIdx.x; e < nnz; e += kSmallThreads) L.col[e] = (uint16_t)ctx.col[e];
@@ -266,12 +270,50 @@ __global__ void __launch_bounds__(kSmallThreads) k_small(Ctx ctx, SmallArgs A) {
   }
   __syncthreads();
   if (W && ctx.ring) {
-    // Theorem 1's bound on the row sums (an unweighted row is short enough)
+    // Theorem 1's bound on the row sums (an unweighted row is short enough):
+    // rows as in the image below, the longest ones by all threads, their sums
+    // added up in x.  (By one thread each, a row of 130,000 entries took 7.4 ms.)
+    const uint32_t lane = lane_id();
+    auto above = [](uint64_t sum) { return sum > (1ull << 32); };
     for (uint32_t i = threadIdx.x; i < n; i += kSmallThreads) {
+      const uint32_t b = L.rp[i], len = L.rp[i + 1] - b;
+      if (len > kSmallHalf) {
+        L.cnt[kSmallNodes - 1 - atomicAdd(&L.nlong, 1u)] = i;
+        L.x[i] = 0;
+        continue;
+      }
+      if (len > kSmallLane) {
+        L.cnt[atomicAdd(&L.nmid, 1u)] = i;
+        continue;
+      }
       uint64_t sum = 0;
-      for (uint32_t e = L.rp[i]; e < L.rp[i + 1]; ++e) sum += ctx.wgt[e];
-      if (sum > (1ull << 32)) L.bad = 1;
+      for (uint32_t t = 0; t < len; ++t) sum += ctx.wgt[b + t];
+      if (above(sum)) L.bad = 1;
     }
+    __syncthreads();
+    const uint32_t nmid = L.nmid, nlong = L.nlong;
+    constexpr uint32_t G = 16;
+    // the bound is the same for the whole wave
+    for (uint32_t t0 = threadIdx.x / kWave * (kWave / G); t0 < nmid; t0 += kSmallThreads / G) {
+      const uint32_t t = t0 + lane / G;
+      const uint32_t i = t < nmid ? L.cnt[t] : 0u;
+      const uint32_t b = L.rp[i], len = t < nmid ? L.rp[i + 1] - b : 0u;
+      uint64_t sum = 0;
+      for (uint32_t e = lane % G; e < len; e += G) sum += ctx.wgt[b + e];
+      for (int off = G / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+      if (above(sum)) L.bad = 1;
+    }
+    for (uint32_t t = 0; t < nlong; ++t) {
+      const uint32_t i = L.cnt[kSmallNodes - 1 - t];
+      const uint32_t b = L.rp[i], len = L.rp[i + 1] - b;
+      uint64_t sum = 0;
+      for (uint32_t e = threadIdx.x; e < len; e += kSmallThreads) sum += ctx.wgt[b + e];
+      for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+      if (lane == 0) atomicAdd((unsigned long long*)&L.x[i], (unsigned long long)sum);
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < nlong; t += kSmallThreads)
+      if (above(L.x[L.cnt[kSmallNodes - 1 - t]])) L.bad = 1;
     __syncthreads();
     if (L.bad) {
       if (threadIdx.x == 0) {

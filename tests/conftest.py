@@ -19,3 +19,12 @@ def gpu_device():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     return torch.device("cuda:0")
+
+
+@pytest.fixture(params=["default", "general"])
+def in_core_path(request, monkeypatch):
+    """Runs a test of graphs that one workgroup can hold on the path they take
+    by themselves and on the general path."""
+    if request.param == "general":
+        monkeypatch.setenv("WL_SMALL", "0")
+    return request.param

@@ -139,3 +139,29 @@ def test_round_cap_and_errors():
     with wl.precision(wl.WL_PRECISION_RING64), pytest.raises(wl.WlError) as e:
         wl.wl_stable_coloring(_dev(rp, col, wt))
     assert e.value.code == wl.WL_EOVERFLOW
+
+
+@pytest.mark.usefixtures("in_core_path")
+@pytest.mark.parametrize("deg", [1, 32, 33, 512, 513, 1025, 130000])
+def test_row_sum_bound_by_row_length(deg):
+    # three rows of the same length whose weights add up to the bound of
+    # Z/2^64, 2^32; one more in one of them is refused
+    rng = np.random.default_rng(deg)
+    n, rows = (70, 1) if deg > 40000 else (1100, 3)
+    rp = np.concatenate([[0], deg * np.minimum(np.arange(1, n + 1), rows)]).astype(np.uint64)
+    col = rng.integers(0, n, deg * rows).astype(np.uint32)
+    wt = np.full(deg * rows, (1 << 32) // deg if deg > 1 else 0xFFFFFFFF, np.uint32)
+    for r in range(rows if deg > 1 else 0):
+        wt[r * deg + deg // 2] += (1 << 32) - deg * ((1 << 32) // deg)
+        assert int(wt[r * deg:(r + 1) * deg].astype(np.uint64).sum()) == 1 << 32
+    print(f"rows of {deg}", flush=True)
+    with wl.precision(wl.WL_PRECISION_RING64):
+        c, k, r = wl.wl_stable_coloring(_dev(rp, col, wt), None, 3)
+        ref, kr, rr, _, st = oracle.stable_coloring(rp, col, wt, None, 3, q=oracle.RING64)
+        assert st == 0 and (k, r) == (kr, rr)
+        assert np.array_equal(c.cpu().numpy().view(np.uint32), ref)
+        if deg > 1:
+            wt[(rows - 1) * deg + deg - 1] += 1
+            with pytest.raises(wl.WlError) as e:
+                wl.wl_stable_coloring(_dev(rp, col, wt), None, 3)
+            assert e.value.code == wl.WL_EOVERFLOW
