@@ -358,9 +358,8 @@ int wl_stats_get(wl_stats *out);
  *   WL_DEGREE_ROUND=0    no histogram round from one colour.
  *   WL_FRONT=n           symmetric graphs of short rows: frontier rounds, whose
  *                        cost follows what changes, tried from round n on
- *                        (default 12, from 2^18 nodes on 16; 0 never, the
- *                        default while WL_HOST_ROUNDS, WL_ASYNC_PASSES or
- *                        WL_GRAPH is set).
+ *                        (default 16; 0 never, the default while
+ *                        WL_HOST_ROUNDS, WL_ASYNC_PASSES or WL_GRAPH is set).
  *   WL_SMALL=0           graphs of at most 4096 nodes and 2^17 entries take
  *                        the general path too, not the one-workgroup one (as
  *                        they do while WL_VALIDATE or a tuning variable of

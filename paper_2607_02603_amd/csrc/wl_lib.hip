@@ -635,13 +635,13 @@ __global__ void __launch_bounds__(kBlock) k_position_colors(Ctx ctx) {
 
 constexpr uint32_t kHostRounds = 8;
 // Rounds before frontier rounds are tried: most graphs are stable by then, and
-// the change costs two to three full rounds.  A call that ends right after a
-// change in vain takes about 1.1 times as long (1000 paths of 28 nodes, 14
-// rounds), so the larger graphs, whose rounds cost more than their launches,
-// wait longer (2^18 nodes: a grid of 35 rounds on 4900 nodes gains 10 % from
-// the earlier one, the 1024 x 1024 grid of 512 rounds 2 %).
-constexpr uint32_t kFrontFrom = 12, kFrontFromLarge = 16;
-constexpr uint64_t kFrontLarge = 1ull << 18;
+// the change costs two to three full rounds, so that a call that ends soon
+// after it has paid for nothing.  Full rounds only / tried from round 12 on /
+// from 16 on, ms: 1000 paths of 28 nodes (14 rounds) 1.42 / 1.76 / 1.40, of 32
+// (16) 1.66 / 1.79 / 1.56, of 36 (18) 1.71 / 1.82 / 2.08, of 40 (20) 2.01 /
+// 1.86 / 2.10, of 60 (30) 2.95 / 2.19 / 2.46; 8000 paths of 32 1.91 / 1.93 /
+// 1.82; 100 x 100 grid (50 rounds) 3.96 / 2.77 / 3.06.
+constexpr uint32_t kFrontFrom = 16;
 // Rounds until the next try, doubled whenever fewer frontier rounds ran than
 // make up for the change.
 constexpr uint32_t kFrontWait = 16, kFrontPays = 4;
@@ -1794,7 +1794,10 @@ struct Session {
       }
       if (!live_built)
         if (int r = build_live_now()) return r;
-      const uint32_t ahead = std::min<uint32_t>(2 * (1 + (groups + 1) / 2), 64);
+      uint32_t ahead = std::min<uint32_t>(2 * (1 + (groups + 1) / 2), 64);
+      // no further than where frontier rounds are tried (rounds go in pairs)
+      if (front_next > host.round)
+        ahead = std::min<uint32_t>(ahead, (front_next - host.round + 1) & ~1u);
       ++groups;
       if (int r = launch_async_rounds(host.round, ahead)) return r;
       if (int r = pull()) return r;
@@ -1889,8 +1892,7 @@ int open_session(Session& S, const wl_csr* g, uint32_t* colors, void* ws,
   {
     // the tuning of the device-driven full rounds keeps them the rounds that run
     const bool tuned = getenv("WL_HOST_ROUNDS") || getenv("WL_ASYNC_PASSES") || S.use_graph;
-    const uint32_t from = g->n < kFrontLarge ? kFrontFrom : kFrontFromLarge;
-    S.front_from = (uint32_t)env_int("WL_FRONT", 0, 1 << 30, tuned ? 0 : (int)from);
+    S.front_from = (uint32_t)env_int("WL_FRONT", 0, 1 << 30, tuned ? 0 : (int)kFrontFrom);
   }
   if (wants_pb(g) && S.pb_mode != 0) {
     S.P = make_pb_layout(g->n, g->nnz);

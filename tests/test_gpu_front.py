@@ -181,8 +181,8 @@ def _strip(width, layers, deg):
 def test_image_of_a_later_full_round_is_chosen_by_its_own_rows():
     # Labels of their own on the first layer: a layer of 8400 nodes becomes
     # singletons in every round, more at once than a workgroup splits, so both
-    # attempts at frontier rounds (from round 12 or 16 on, and 17 rounds later) go back
-    # at once.  The propagation-blocking image serves rounds 0 to 7 and the
+    # attempts at frontier rounds (from round 16 on, and 17 rounds later) go
+    # back at once.  The propagation-blocking image serves rounds 0 to 7 and the
     # full round of the first attempt, while at least half of the entries feed
     # rows that need one; by the second attempt fewer do.
     width, layers = 8400, 50
