@@ -1366,11 +1366,12 @@ struct Session {
                          s, ctx, kImgUniform, 1);
     timed_spmv(host.round, true, kImgUniform, [&] {
       hipLaunchKernelGGL(k_deg_clear, dim3(gd), dim3(kBlock), 0, s, ctx, d, maxd);
-      // every workgroup ends by adding its counts to the same few counters
-      // (R-MAT 22: 70 us with 4096 workgroups, 23 with 512); larger graphs need
-      // more loads in flight (R-MAT 27: 633 us with 512, 599 with 1024)
+      // every workgroup ends by adding its counts to the same few counters;
+      // larger graphs need more loads in flight (us with 512 / 1024 / 4096
+      // workgroups: R-MAT 22 29 / 36 / 76, 23 35 / 40 / 88, 24 55 / 57 / 94, 25
+      // 96 / 91 / 109; R-MAT 27 633 with 512, 599 with 1024)
       hipLaunchKernelGGL(k_deg_hist<RP64>,
-                         dim3(grid_for(L.n, kDegStep * kBlock, L.n < (1ull << 24) ? 512 : 1024)),
+                         dim3(grid_for(L.n, kDegStep * kBlock, L.n < (1ull << 25) ? 512 : 1024)),
                          dim3(kBlock), 0, s, ctx, d);
     });
     hipLaunchKernelGGL(k_deg_list, dim3(gd), dim3(kBlock), 0, s, ctx, d, maxd);
