@@ -58,6 +58,7 @@ def _check_exact(rp, col, wt=None, init=None, seed=0, rp64=False, classic=True):
 # small graphs, every shape of row and class
 # ---------------------------------------------------------------------------
 
+@pytest.mark.usefixtures("in_core_path")
 @pytest.mark.parametrize("trial", range(24))
 def test_random_small_graphs(trial):
     rng = random.Random(trial)
@@ -82,6 +83,7 @@ def test_random_small_graphs(trial):
     _check_exact(rp, col, wt, init, seed=trial, rp64=trial % 2 == 0)
 
 
+@pytest.mark.usefixtures("in_core_path")
 @pytest.mark.parametrize("n", [1, 2, 3, 17])
 def test_edgeless(n):
     rp = np.zeros(n + 1, np.uint64)
@@ -96,6 +98,7 @@ def test_empty_graph():
     assert (k, r) == (0, 0)
 
 
+@pytest.mark.usefixtures("in_core_path")
 def test_path_and_grid_closed_forms():
     for n in (2, 5, 12, 101):
         rp, col = bf.to_csr(n, [(i, i + 1) for i in range(n - 1)])
@@ -159,6 +162,7 @@ def test_initial_colours_large_labels():
     _check_exact(g.row_ptr, g.col, init=init, seed=2)
 
 
+@pytest.mark.usefixtures("in_core_path")
 def test_weighted_quotient_like_graph():
     rng = random.Random(8)
     n = 3000
@@ -262,6 +266,7 @@ def test_config_grid_1024():
 # errors
 # ---------------------------------------------------------------------------
 
+@pytest.mark.usefixtures("in_core_path")
 def test_errors():
     g = inputs.er_graph(1000, 3000, seed=1)
     dg = _dev_graph(g.row_ptr, g.col)

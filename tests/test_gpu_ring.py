@@ -64,6 +64,7 @@ def _exact(rp, col, wt=None, init=None, seed=0, rp64=False, symmetric=False, cla
     return got, k, r
 
 
+@pytest.mark.usefixtures("in_core_path")
 @pytest.mark.parametrize("trial", range(16))
 def test_random_small_graphs(trial):
     rng = random.Random(300 + trial)
@@ -84,6 +85,7 @@ def test_random_small_graphs(trial):
     _exact(rp, col, wt, init, seed=trial)
 
 
+@pytest.mark.usefixtures("in_core_path")
 def test_path_grid_and_edgeless():
     for n in (1, 2, 5, 12, 101):
         rp, col = bf.to_csr(n, [(i, i + 1) for i in range(n - 1)])
@@ -161,6 +163,7 @@ def test_many_colours_full_table_mode():
     assert k > 65535
 
 
+@pytest.mark.usefixtures("in_core_path")
 def test_weighted_quotient_like_graph():
     rng = random.Random(8)
     n = 3000
@@ -315,6 +318,7 @@ def test_batched_weighted_directed():
 # Theorem 1's bound on the row sums
 # ---------------------------------------------------------------------------
 
+@pytest.mark.usefixtures("in_core_path")
 def test_row_sum_bound_every_path():
     rp = np.array([0, 3, 3, 4], np.uint64)
     col = np.array([1, 1, 2, 0], np.uint32)
@@ -334,7 +338,8 @@ def test_row_sum_bound_every_path():
     with pytest.raises(wl.WlError) as e:
         wl.wl_stable_coloring_batched(_host_graph(rp, col, bad), None, 0, 2)
     assert e.value.code == wl.WL_EOVERFLOW
-    # a row of 100 weights (summed by a whole wave) at and above the bound
+    # a row of 100 weights at and above the bound (summed by a whole wave on the
+    # general path, by one thread on the one-workgroup path)
     n = 101
     rp = np.array([0, 100] + [100] * (n - 1), np.uint64)
     col = np.arange(1, 101, dtype=np.uint32)

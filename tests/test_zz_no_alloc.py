@@ -44,6 +44,7 @@ def _same(dg, init=None, seed=0, label=""):
     return c, k, r
 
 
+@pytest.mark.usefixtures("in_core_path")
 def test_consecutive_calls_shrinking_inputs():
     big = inputs.rmat(16, 8, seed=1)
     small = inputs.rmat(10, 4, seed=2)
@@ -57,6 +58,7 @@ def test_consecutive_calls_shrinking_inputs():
     assert np.array_equal(c.cpu().numpy().view(np.uint32), ref)
 
 
+@pytest.mark.usefixtures("in_core_path")
 def test_consecutive_calls_labels_seeds_symmetric():
     grid = inputs.grid_graph(40, 50)
     er = inputs.er_graph(3000, 9000, seed=4)
