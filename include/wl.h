@@ -89,9 +89,13 @@ extern "C" {
  * LDS-sized bins (streaming passes) instead of one random read per entry;
  * this needs the larger workspace wl_workspace_size() reports for such a
  * graph (4 to 8 bytes more per entry) and is skipped when the workspace is
- * smaller.  A graph flagged symmetric that is not is reported as WL_EINVAL
- * when the library notices (it checks the entry counts per bin of rows;
- * results are defined only for correctly flagged graphs). */
+ * smaller.  For a symmetric graph of short rows, weighted or not and of any
+ * number of entries, they may run frontier rounds (see WL_FRONT), which find
+ * the nodes that a split can reach by walking the rows.  A graph flagged
+ * symmetric that is not is reported as WL_EINVAL when the library notices (the
+ * bins check their entry counts; frontier rounds, and graphs of at most 4096
+ * nodes, for which the flag has no effect, check nothing): results are defined
+ * only for correctly flagged graphs. */
 #define WL_CSR_SYMMETRIC 1ull
 typedef struct wl_csr {
     uint64_t n;

@@ -14,8 +14,8 @@
 //           colours of this round);
 //   split   every class with marked members: their images and the one image
 //           that all its other members share, taken from one of them; the
-//           distinct images in order are its parts.  The unmarked members stay, the others
-//           get class indices of their own and are the next S;
+//           distinct images in order are its parts.  The unmarked members
+//           stay, the others get class indices of their own and are the next S;
 //   apply   colours are ranks, so a class moves up by the number of parts
 //           added below it: per class, not per node (a node stores its class
 //           index, and a neighbour's value is W(color[class])).
@@ -212,7 +212,8 @@ __global__ void __launch_bounds__(kBlock) k_front_seed(Ctx ctx, FrontCtx F) {
   __shared__ uint32_t sh[kBlock / kWave];
   __shared__ uint32_t base_sh;
   const uint32_t k = ctx.st->k;
-  for (uint64_t p0 = (uint64_t)blockIdx.x * kBlock; p0 < ctx.n; p0 += (uint64_t)gridDim.x * kBlock) {
+  for (uint64_t p0 = (uint64_t)blockIdx.x * kBlock; p0 < ctx.n;
+       p0 += (uint64_t)gridDim.x * kBlock) {
     const uint64_t p = p0 + threadIdx.x;
     bool in = false;
     uint32_t v = 0;
@@ -935,7 +936,7 @@ __global__ void __launch_bounds__(kBlock) k_front_apply(Ctx ctx, FrontCtx F, uin
     nxt->done = round + 1 >= ctx.st->max_rounds ? 2u : 0u;
   }
   __shared__ uint32_t sh[kBlock / kWave];
-  __shared__ uint32_t wide[kFrontChunk], wide_at[kFrontChunk];  // colours of many parts, old and new
+  __shared__ uint32_t wide[kFrontChunk], wide_at[kFrontChunk];  // colours of many parts: old, new
   __shared__ uint32_t nwide;
   const uint64_t key = round_key(ctx.st->seed, round + 1);
   const uint32_t* ord = F.ord[i & 1];

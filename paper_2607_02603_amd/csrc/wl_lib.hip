@@ -1813,11 +1813,11 @@ struct Session {
 
   // A graph that one workgroup's LDS holds goes through wl_small.h whole: the
   // general path took 0.69 ms for 1500 nodes and 12,000 entries (0.43 ms for
-  // 20,000 nodes and 160,000 entries), this one 0.07 ms.  The bounds are the LDS (nodes) and where
-  // one compute unit's loads of the columns cost as much as the general
-  // path's launches (entries).  WL_SMALL=0, the tuning variables of the
-  // general path, validation and the diagnostics (which describe its image
-  // launches) keep a graph on the general path.
+  // 20,000 nodes and 160,000 entries), this one 0.07 ms.  The bounds are the
+  // LDS (nodes) and where one compute unit's loads of the columns cost as much
+  // as the general path's launches (entries).  WL_SMALL=0, the tuning
+  // variables of the general path, validation and the diagnostics (which
+  // describe its image launches) keep a graph on the general path.
   bool small_applies(bool diag) const {
     if (L.n > kSmallNodes || L.nnz > kSmallEntries || (diag && g_stats_flags)) return false;
     static const char* const names[] = {"WL_VALIDATE",    "WL_PB",          "WL_DEGREE_ROUND",

@@ -73,11 +73,12 @@ struct PbCtx {
   uint64_t* bstart1;   // nb1 + 1: first entry of the rows of each pass-1 bin
   uint64_t* bstartf;   // nfine + 1: the same for the fine bins
   uint32_t* rec1;      // pass-1 records (coarse bins; levels == 2)
-  uint32_t* rec2;      // fine-bin records
+  uint32_t* rec2;      // the records that pass 3 reads: fine bins, or (half) bins of two
   uint32_t* tile_row;  // ntiles1: row that holds the first entry of each tile
   uint32_t* tile2_off; // nb1 + 1: pass-2 tiles before each coarse bin
-  unsigned long long* cur1;  // nb1: write cursors of pass 1 (levels == 2)
+  unsigned long long* cur1;  // nb1: write cursors of pass 1 (levels == 2, or half)
   unsigned long long* cur2;  // nfine: write cursors of the fine bins
+                             // (half: records that pass 3 found, see k_pb_check_halves)
   uint32_t* slice_off;       // nfine + 1: pass-3 items before each fine bin
   uint32_t* mslice_off;      // nfine + 1: partial-sum slots before each bin
   uint32_t* mlist;           // fine bins with several slices

@@ -2,12 +2,12 @@
 //
 // A graph of a few thousand nodes gives the chip nothing to do: a call of the
 // general path was about 90 launches and 14 read-backs, 0.65 ms whatever the
-// size (0.43 ms with one read-back a round).  Here one workgroup of 1024 threads holds the colouring in LDS and
-// runs every round in one launch, so a call costs the launch, one read-back
-// and a few microseconds of LDS work per round (bound by the chain of
-// workgroup barriers).  It computes what the general path computes: z = A w
-// in exact arithmetic for every node of a class of two or more, new colour =
-// rank of (colour, z).
+// size (0.43 ms with one read-back a round).  Here one workgroup of 1024
+// threads holds the colouring in LDS and runs every round in one launch, so a
+// call costs the launch, one read-back and a few microseconds of LDS work per
+// round (bound by the chain of workgroup barriers).  It computes what the
+// general path computes: z = A w in exact arithmetic for every node of a class
+// of two or more, new colour = rank of (colour, z).
 //
 // State (positions p = 0 .. n - 1, sorted by class):
 //   node[p]  node at the position

@@ -4,8 +4,8 @@ H on which z is symmetric": the ranks of (c, z) by lexicographic sorting).
 A class of 65 to 2048 members is sorted in LDS by a counting sort on ten bits
 of z (a workgroup per segment; segments of at most 512 take one wave each
 with nine bits when a round has at least 1024 of them); a bucket whose keys
-differ is fixed by an insertion sort when it holds at most WL_SORT_FIX keys
-(default 32), and the whole segment otherwise goes to a bitonic network.
+differ is ranked by pairs when it holds at most WL_SORT_FIX keys (default
+32), and the whole segment otherwise goes to a bitonic network.
 WL_SORT_FIX=0 sends every segment with a mixed bucket to the network, so
 all paths give the oracle's colours, colour count and round count bit for
 bit, in F_p and in Z/2^64.
